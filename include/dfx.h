@@ -330,10 +330,10 @@ int dfx_group_get(dfx_ctx* ctx, int64_t i, dfx_group_info* out);
  * stops early once *conv_a <= tol * *conv_b (two 0-d FP64 stores of the
  * context, compared in FP64 after each repetition; conv_a = conv_b = 0: no
  * test).  dfx_batch_run launches one persistent kernel over every stream:
- * waves claim (stream, pass, tile run) work items from per-stream claim
- * counters, and the wave that completes a pass's last run reduces its tile
+ * blocks claim (stream, pass, tile run) work items from per-stream claim
+ * counters, and the block that completes a pass's last run reduces its tile
  * sums with the same canonical tree as the ordinary path and advances the
- * stream; no wave waits on another.  Every result is therefore bit-identical
+ * stream; no block waits on another.  Every result is therefore bit-identical
  * to the same stream run through dfx_flush.
  * Limits: FP64 passes of at most 8 live values and 6 input streams (tiers
  * with more registers or pow give DFX_EUNSUPPORTED at record_end) and at most

@@ -18,9 +18,9 @@
 
 namespace dfx {
 
-int launch_batch(const BatchPass* passes, BatchStream* streams, BatchCtl* ctl, int grid, int heavy,
+int launch_batch(const BatchPass* passes, BatchStream* streams, BatchCtl* ctl, int grid, int heavy, uint32_t lds,
                  hipStream_t stream);
-int batch_waves_per_cu(int heavy);
+int batch_blocks_per_cu(int heavy, uint32_t lds);
 
 struct BatchRec {
   dfx_batch* b = nullptr;
@@ -53,7 +53,7 @@ struct dfx_batch {
   bool started = false;
   bool pending = false;   // a launch not yet waited for
   int grid = 0;
-  int grid_hv[2] = {0, 0};   // resident blocks of the arithmetic / transcendental kernel
+  int n_cu = 0;
   int n_xcd = 1;          // XCDs (L2 domains) of the device; stream s runs on XCD s % n_xcd
   std::string err;
 };
@@ -125,12 +125,12 @@ int dfx_batch_create(int32_t device, void* stream, dfx_batch** out) {
     delete b;
     return DFX_EHIP;
   }
-  // every block resident; gfx950 has 32 compute units per XCD, and blocks
-  // are dispatched to the XCDs in turn, so each XCD gets grid / n_xcd of them
+  // one block of 16 waves per compute unit, every one resident; gfx950 has
+  // 32 compute units per XCD, and blocks are dispatched to the XCDs in turn,
+  // so each XCD gets grid / n_xcd of them
   b->n_xcd = std::max(1, std::min(BATCH_MAX_XCD, n_cu / 32));
-  for (int h = 0; h < 2; ++h)
-    b->grid_hv[h] = std::max(b->n_xcd, n_cu * std::max(batch_waves_per_cu(h), 4) / (BLOCK / WAVE));
-  b->grid = b->grid_hv[1];
+  b->n_cu = n_cu;
+  b->grid = std::max(b->n_xcd, n_cu);
   *out = b;
   return DFX_OK;
 }
@@ -292,6 +292,15 @@ int dfx_batch_run(dfx_batch* b, int32_t round_limit, int32_t restart) {
   b->ctl.n_streams = (uint32_t)ns;
   b->ctl.n_xcd = (uint32_t)b->n_xcd;
   b->ctl.round_limit = std::max(0, round_limit);
+  int max_red = 0;
+  bool spmv = false;
+  for (const BatchPass& B : b->passes) {
+    max_red = std::max(max_red, (int)B.P.n_red);
+    spmv = spmv || B.P.spmv != 0;
+  }
+  const CoopLds lds = coop_lds(max_red, spmv);
+  b->ctl.lds_slots = lds.slots;
+  b->ctl.lds_staged = lds.staged;
   for (size_t i = 0; i < ns; ++i) {
     BatchXcd& X = b->ctl.x[i % b->n_xcd];
     X.n_streams += 1;
@@ -305,8 +314,8 @@ int dfx_batch_run(dfx_batch* b, int32_t round_limit, int32_t restart) {
     return bfail(b, DFX_EHIP, "batch state upload");
   if (settled == ns) return DFX_OK;
   const int heavy = std::find(b->pass_heavy.begin(), b->pass_heavy.end(), 1) != b->pass_heavy.end() ? 1 : 0;
-  b->grid = b->grid_hv[heavy];
-  const int e = launch_batch(b->d_passes, b->d_streams, b->d_ctl, b->grid, heavy, b->stream);
+  if (batch_blocks_per_cu(heavy, lds.bytes) < 1) return bfail(b, DFX_EHIP, "the batch kernel does not fit a compute unit");
+  const int e = launch_batch(b->d_passes, b->d_streams, b->d_ctl, b->grid, heavy, lds.bytes, b->stream);
   if (e != 0) return bfail(b, DFX_EHIP, std::string("batch launch: ") + hipGetErrorString((hipError_t)e));
   b->pending = true;
   return DFX_OK;

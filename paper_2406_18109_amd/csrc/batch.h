@@ -5,10 +5,10 @@
 // passes [pass0, pass0 + n_pre) run once, then [pass0 + n_pre,
 // pass0 + n_pre + n_body) repeat up to max_iter times, stopping early when a
 // 0-d FP64 value falls to tol times another.  One persistent launch runs every
-// stream: each wave repeatedly claims a work item (stream, current pass, tile
-// run) of a stream of its XCD and executes it; the wave that finishes a
+// stream: each block repeatedly claims a work item (stream, current pass, tile
+// run) of a stream of its XCD and executes it; the block that finishes a
 // pass's last run reduces the pass's tile sums with the canonical tree and
-// advances the stream.  No wave waits for another: a wave with nothing to
+// advances the stream.  No block waits for another: a block with nothing to
 // claim looks at the XCD's other streams.
 #pragma once
 #include <stdint.h>
@@ -61,6 +61,7 @@ struct BatchCtl {
   int32_t round_limit;           // > 0: a stream pauses after this many repetitions in one launch
   uint32_t xcc_seen;             // bit k: some wave ran on XCD k (diagnostics)
   uint32_t waves[16];            // waves that started, per XCD id (diagnostics)
+  int32_t lds_slots, lds_staged; // the blocks' dynamic LDS (coop_lds)
 };
 
 }  // namespace dfx

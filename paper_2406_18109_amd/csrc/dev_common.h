@@ -33,30 +33,30 @@ template <typename T> __device__ void lds_tree(T* a, int L) {
 
 
 // Row i of y = A x for a CSR matrix: summed sequentially in CSR order
-// (s = a0*x0, then s = s + ak*xk), nonzeros fetched eight at a time so that
+// (s = a0*x0, then s = s + ak*xk), nonzeros fetched D at a time so that
 // several gathers are in flight.  Row pointers are clamped to [0, nnz] and
 // column indices to [0, nx): a malformed matrix yields wrong values, never an
 // access outside the arrays.
-template <typename T>
+template <typename T, int D = 8>
 __device__ __forceinline__ T csr_row(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
                                      const T* __restrict__ val, const T* __restrict__ x, int64_t i, int32_t nnz,
                                      uint32_t nx) {
   const int32_t rb = min(max(rowptr[i], 0), nnz);
   const int32_t re = min(max(rowptr[i + 1], rb), nnz);
   T s = (T)0;
-  for (int32_t k = rb; k < re; k += 8) {
-    int32_t c[8];
-    T a[8], xv[8];
+  for (int32_t k = rb; k < re; k += D) {
+    int32_t c[D];
+    T a[D], xv[D];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < D; ++j) {
       const int32_t idx = k + j < re ? k + j : rb;
       c[j] = colidx[idx];
       a[j] = val[idx];
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) xv[j] = x[(uint32_t)c[j] < nx ? c[j] : 0];
+    for (int j = 0; j < D; ++j) xv[j] = x[(uint32_t)c[j] < nx ? c[j] : 0];
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < D; ++j)
       if (k + j < re) {
         const T t = a[j] * xv[j];
         s = (k + j == rb) ? t : s + t;

@@ -137,10 +137,11 @@ template <typename T, int NG, int GS> struct VmState {
   typedef typename GVec<T, GS>::type gvec;
   gvec z[NG];               // previous instruction's result (forwarded operand)
   T acc0, acc1, acc2, acc3; // this lane's reduction accumulators
-  // A tile shared by a block's waves (compiled passes, red_split): reduction
-  // slot 0 writes its summands to dsum[(drow + u) * TW + lane * V + v] (drow:
-  // the step's first row within the tile) instead of accumulating them.
-  // Set by compiled kernels only (the interpreter never reads them).
+  // A tile shared by a block's waves (compiled passes under red_split,
+  // coop_tile): a reduction writes its summands to dsum[slot * RED_TH * TW +
+  // (drow + u) * TW + lane * V + v] (drow: the step's first row within the
+  // tile) instead of accumulating them.  The interpreter's one-wave tiles
+  // never read them.
   T* dsum;
   int drow;
 };
@@ -663,29 +664,45 @@ template <typename T> __device__ __forceinline__ T block_tree(const T* a, int cn
 // not valid is read and not added).  The additions are one dependent chain;
 // loading each element when its turn comes put 32 memory latencies into that
 // chain as well (15.5 us for the scalar pass after a dot product over 4096
-// elements, against 5.5 us this way), so half a tile's vectors are loaded first,
-// all in flight together, then added.
-template <typename T>
+// elements, against 5.5 us this way), so H rows' vectors are loaded first,
+// all in flight together, then added (H: 16 from global memory, 8 from LDS).
+template <typename T, int H>
 __device__ __forceinline__ T tile_lane_sum(const T* ds, const int lane, const int is1d, const int64_t row0,
                                            const int64_t n1d, const int64_t rows, const int64_t cols,
                                            const int64_t c0) {
-  constexpr int V = Lanes<T>::V, TW = Lanes<T>::TW, H = RED_TH / 2;
+  constexpr int V = Lanes<T>::V, TW = Lanes<T>::TW;
   typedef T vecA __attribute__((ext_vector_type(V)));
-  T acc = (T)0;
+  // element v of the lane is valid in the first rl[v] rows
+  int rl[V];
+  bool whole = true;
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
+  for (int v = 0; v < V; ++v) {
+    const int64_t col = c0 + (int64_t)lane * V + v;
+    const int64_t left = is1d ? (n1d - col + TW - 1) / TW - row0 : col >= 0 && col < cols ? rows - row0 : 0;
+    rl[v] = (int)max((int64_t)0, min((int64_t)RED_TH, left));
+    whole = whole && rl[v] == RED_TH;
+  }
+  const bool all = __ballot(whole) == ~0ull;
+  T acc = (T)0;
+#pragma unroll 1
+  for (int h = 0; h < RED_TH; h += H) {
     vecA w[H];
 #pragma unroll
-    for (int r = 0; r < H; ++r) w[r] = *(const vecA*)(ds + (h * H + r) * TW + lane * V);
+    for (int r = 0; r < H; ++r) w[r] = *(const vecA*)(ds + (h + r) * TW + lane * V);
+    if (all) {
 #pragma unroll
-    for (int r = 0; r < H; ++r)
+      for (int r = 0; r < H; ++r)
 #pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const int64_t row = row0 + h * H + r, col = c0 + (int64_t)lane * V + v;
-        const bool ok = is1d ? (row * TW + col < n1d) : (row < rows && col >= 0 && col < cols);
-        const T s = acc + w[r][v];
-        acc = ok ? s : acc;
-      }
+        for (int v = 0; v < V; ++v) acc = acc + w[r][v];
+    } else {
+#pragma unroll
+      for (int r = 0; r < H; ++r)
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          const T s = acc + w[r][v];
+          acc = h + r < rl[v] ? s : acc;
+        }
+    }
   }
   return acc;
 }
@@ -714,7 +731,7 @@ template <typename T, int NW, int MAXCH> __device__ __forceinline__ void fin_sum
     // rows, then columns (valid elements only), then across lanes, as the
     // wave that owns a tile accumulates them
     if (w != 0) return;
-    const T acc = tile_lane_sum<T>((const T*)F.partials[0], lane, F.is1d, 0, F.n1d, F.rows, F.cols,
+    const T acc = tile_lane_sum<T, 16>((const T*)F.partials[0], lane, F.is1d, 0, F.n1d, F.rows, F.cols,
                                    -(int64_t)F.col_shift);
     const T total = wave_sum(acc);
     if (lane == 0) {
@@ -1071,7 +1088,7 @@ void vm_kernel(const VmParams P) {
       extern __shared__ __attribute__((aligned(16))) char vm_dyn_lds[];
       const T* ds = (const T*)vm_dyn_lds;
       const int64_t tr = t_begin / P.strips;
-      const T acc = tile_lane_sum<T>(ds, lane, P.is1d, tr * RED_TH, P.n1d, P.rows, P.cols,
+      const T acc = tile_lane_sum<T, 8>(ds, lane, P.is1d, tr * RED_TH, P.n1d, P.rows, P.cols,
                                      (t_begin - tr * P.strips) * TW - P.col_shift);
       const T v = wave_sum(acc);
       if (lane == 0) {
