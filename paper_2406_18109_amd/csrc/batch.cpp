@@ -228,6 +228,16 @@ int dfx_batch_record_end(dfx_batch* b, dfx_ctx* c, int32_t max_iter, dfx_store c
   return DFX_OK;
 }
 
+// Runs of the pass a stream executes after `gen` completed ones (0: none).
+static uint32_t first_runs(const dfx_batch* b, const BatchStream& st, uint32_t gen) {
+  int64_t p = (int64_t)gen;
+  if (p >= st.n_pre) {
+    if (st.n_body == 0) return 0;
+    p = st.n_pre + (int64_t)((gen - (uint32_t)st.n_pre) % (uint32_t)st.n_body);
+  }
+  return (uint32_t)b->passes[st.pass0 + p].n_runs;
+}
+
 // Launch every stream.  restart != 0: every stream starts from its first
 // pass; 0: streams paused by a round limit resume, finished ones stay done.
 int dfx_batch_run(dfx_batch* b, int32_t round_limit, int32_t restart) {
@@ -274,18 +284,19 @@ int dfx_batch_run(dfx_batch* b, int32_t round_limit, int32_t restart) {
   size_t settled = 0;
   for (auto& st : b->streams) {
     if (restart || !b->started) {
-      st.claim = 0;
+      st.claim = claim_word(0, first_runs(b, st, 0), 0);
       st.done = 0;
       st.iters = 0;
       st.status = (st.n_pre == 0 && (st.n_body == 0 || st.max_iter == 0)) ? BS_DONE : BS_RUNNING;
     } else if (st.status == BS_PAUSED) {
       st.status = BS_RUNNING;
-      st.claim = (st.claim >> 32) << 32;   // reopen the next pass
+      const uint32_t gen = (uint32_t)(st.claim >> 32);
+      st.claim = claim_word(gen, first_runs(b, st, gen), 0);   // reopen the next pass
     }
     st.round_iters = 0;
     if (st.status != BS_RUNNING) {
       settled += 1;
-      st.claim = ((st.claim >> 32) << 32) | 0x80000000ull;   // closed: nothing to claim
+      st.claim = claim_word((uint32_t)(st.claim >> 32), 0, 0);   // closed: nothing to claim
     }
   }
   std::memset(&b->ctl, 0, sizeof(b->ctl));
@@ -298,9 +309,7 @@ int dfx_batch_run(dfx_batch* b, int32_t round_limit, int32_t restart) {
     max_red = std::max(max_red, (int)B.P.n_red);
     spmv = spmv || B.P.spmv != 0;
   }
-  const CoopLds lds = coop_lds(max_red, spmv);
-  b->ctl.lds_slots = lds.slots;
-  b->ctl.lds_staged = lds.staged;
+  const uint32_t lds = coop_lds(max_red, spmv);
   for (size_t i = 0; i < ns; ++i) {
     BatchXcd& X = b->ctl.x[i % b->n_xcd];
     X.n_streams += 1;
@@ -314,8 +323,8 @@ int dfx_batch_run(dfx_batch* b, int32_t round_limit, int32_t restart) {
     return bfail(b, DFX_EHIP, "batch state upload");
   if (settled == ns) return DFX_OK;
   const int heavy = std::find(b->pass_heavy.begin(), b->pass_heavy.end(), 1) != b->pass_heavy.end() ? 1 : 0;
-  if (batch_blocks_per_cu(heavy, lds.bytes) < 1) return bfail(b, DFX_EHIP, "the batch kernel does not fit a compute unit");
-  const int e = launch_batch(b->d_passes, b->d_streams, b->d_ctl, b->grid, heavy, lds.bytes, b->stream);
+  if (batch_blocks_per_cu(heavy, lds) < 1) return bfail(b, DFX_EHIP, "the batch kernel does not fit a compute unit");
+  const int e = launch_batch(b->d_passes, b->d_streams, b->d_ctl, b->grid, heavy, lds, b->stream);
   if (e != 0) return bfail(b, DFX_EHIP, std::string("batch launch: ") + hipGetErrorString((hipError_t)e));
   b->pending = true;
   return DFX_OK;

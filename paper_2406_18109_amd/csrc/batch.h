@@ -11,6 +11,7 @@
 // advances the stream.  No block waits for another: a block with nothing to
 // claim looks at the XCD's other streams.
 #pragma once
+#include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "vm.h"
@@ -18,6 +19,20 @@
 namespace dfx {
 
 constexpr int BATCH_MAX_RUNS = 4096;  // work items per pass (runs of tiles_per_wave tiles)
+
+// A stream's claim word: passes completed << 32 | runs of the current pass
+// << 16 | next run to claim, so that one load tells whether a run is left.
+// A settled (done or paused) stream has no runs.  Claimers add one after
+// seeing a run left, so the next-run field passes the runs by at most one
+// per block of the launch and never reaches the runs field.  While a block
+// keeps a stream to itself (passes of one run) the word stays that of the
+// last published pass, all of whose runs are taken.
+__host__ __device__ inline unsigned long long claim_word(uint32_t gen, uint32_t runs, uint32_t next) {
+  return (unsigned long long)gen << 32 | (unsigned long long)runs << 16 | next;
+}
+__host__ __device__ inline bool claimable(unsigned long long w) {
+  return ((uint32_t)w & 0xffffu) < ((uint32_t)w >> 16);
+}
 
 struct BatchPass {
   VmParams P;                    // red_partials unused: tile sums go to the stream's tsum
@@ -36,7 +51,7 @@ struct BatchStream {
   double* tsum;                  // tile sums: [VM_MAXRED][tsum_stride], then one chunk-sum row
   int64_t tsum_stride;
   // device state, kept across launches
-  unsigned long long claim;      // (passes completed << 32) | next run to claim
+  unsigned long long claim;      // claim_word
   uint32_t done;                 // runs finished of the current pass
   int32_t iters;                 // repetitions of the body completed
   int32_t round_iters;           // repetitions completed in this launch
@@ -61,7 +76,6 @@ struct BatchCtl {
   int32_t round_limit;           // > 0: a stream pauses after this many repetitions in one launch
   uint32_t xcc_seen;             // bit k: some wave ran on XCD k (diagnostics)
   uint32_t waves[16];            // waves that started, per XCD id (diagnostics)
-  int32_t lds_slots, lds_staged; // the blocks' dynamic LDS (coop_lds)
 };
 
 }  // namespace dfx

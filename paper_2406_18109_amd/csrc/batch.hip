@@ -8,16 +8,19 @@
 // the two-launch path evaluates, so every result is bit-identical to a solo
 // run), writes the 0-d results, advances the stream to its next pass and
 // takes that pass's first run itself.  A stream runs on one XCD; its passes
-// are ordered by agent-scope release/acquire (xcd_release, xcd_acquire);
+// are ordered by agent-scope release/acquire (xcd_release, block_acquire);
 // values written inside the launch (0-d results, tile sums) are read with
 // vector or atomic loads, never through the scalar cache.
 //
 // What bounds it is the latency of a pass: claim, acquire, the pass's
-// dependent loads, release, count, publish.  With single waves as workers a
-// tile was one wave's 32 rows in sequence and every idle wave of the chip
-// polled the claim words (about 97 us per pass of 16 tiles); blocks have a
-// sixteenth of the pollers and of the chain.  Measured over 32 CG solves of
-// sides 32 to 256 to 1e-8: 403 ms with waves as workers, 84 ms with blocks.
+// dependent loads, release, count, publish.  Three things decide it, measured
+// over 32 CG solves of sides 32 to 256 to 1e-8.  With single waves as workers
+// a tile was one wave's 32 rows in sequence and every idle wave of the chip
+// polled the claim words: about 97 us per pass of 16 tiles, 403 ms in all;
+// with blocks 84 ms.  One wave's acquire for its block instead of sixteen:
+// 34 ms.  Passes of one run are kept by the block that completed the pass
+// before: no claim, and no wait for stores, between them (a one-tile CG
+// iteration of five passes takes 18 us at 256 unknowns, 27 us at 4096).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -50,7 +53,12 @@ __device__ __forceinline__ void xcd_release() {
   __builtin_amdgcn_s_waitcnt(0);
   asm volatile("" ::: "memory");
 }
-__device__ __forceinline__ void xcd_acquire() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); }
+// By one wave, before a block barrier: for every wave of the block.
+__device__ __forceinline__ void block_acquire() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  __builtin_amdgcn_s_waitcnt(0);
+  asm volatile("" ::: "memory");
+}
 template <typename U> __device__ __forceinline__ U xload(U* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -60,13 +68,6 @@ template <typename U> __device__ __forceinline__ void xstore(U* p, U v) {
 template <typename U> __device__ __forceinline__ U xadd(U* p, U v) {
   return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// A data word written inside the launch (a 0-d result), read after an
-// acquire: an atomic load, never the scalar cache.
-__device__ __forceinline__ double load_data_f64(const double* p) {
-  return __builtin_bit_cast(double, __hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_AGENT));
-}
-
 __device__ __forceinline__ unsigned long long bcast64(unsigned long long v) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
@@ -80,10 +81,6 @@ __device__ __forceinline__ int pass_of(const BatchStream& st, uint32_t g) {
   if (st.n_body == 0) return -1;
   return st.pass0 + st.n_pre + (int)((g - (uint32_t)st.n_pre) % (uint32_t)st.n_body);
 }
-
-// Run index a settled (done or paused) stream's claim word holds: never
-// claimable, and far from carrying into the pass count.
-constexpr unsigned long long CLAIM_CLOSED = 0x80000000ull;
 
 // The canonical tree over a[0..n) (any n >= 1) evaluated by one wave:
 // aligned chunks of 256 are complete subtrees (block_tree), their sums are
@@ -115,10 +112,12 @@ __device__ double wave_tree(const double* a, int64_t n, double* scratch, int lan
 #define DFX_BATCH_STALL_TICKS 200000000ull
 #endif
 
-// What wave 0 found for its block.
+// What wave 0 found, or decided, for its block.
 struct BatchItem {
-  int32_t sid, pidx;   // sid < 0: leave
+  int32_t sid, pidx;   // sid < 0: leave; pidx < 0: nothing taken, search
   uint32_t run, gen;
+  int32_t status;      // the stream's after a completed pass
+  int32_t publish;     // ... whose next pass other blocks may claim (or that has settled)
 };
 
 template <int BHV>
@@ -142,20 +141,69 @@ __global__ __launch_bounds__(COOP_BLOCK) void batch_kernel(const BatchPass* __re
   BatchXcd& X = ctl->x[xcc];
   const uint32_t ns = X.n_streams;   // streams xcc, xcc + nxcd, ...
   if (ns == 0) return;
-  const int slots = ctl->lds_slots, staged = ctl->lds_staged;
-  // (wave 0 alone searches; these are its own)
+  // (wave 0 alone searches and decides; these are its own)
   uint32_t s = (blockIdx.x / nxcd) % ns;   // index among this XCD's streams
   uint32_t seen_progress = 0;
   unsigned long long since = __builtin_amdgcn_s_memrealtime();
-  bool have = false;   // item holds the run this block took when it published the pass
+  int32_t own_it = -1, own_rit = 0;   // the stream's repetition counts while this block keeps it (-1: not known)
+  bool have = false;                  // item holds a run this block took when it completed a pass
   // stream and pass up to which this block's last acquire made every earlier
   // pass visible (passes before acq_gen of stream acq_sid)
   int acq_sid = -1;
   uint32_t acq_gen = 0;
   for (;;) {
     if (wib == 0 && !have) {
-      BatchItem it = {-1, 0, 0u, 0u};
+      BatchItem it = {-1, -1, 0u, 0u, BS_RUNNING, 0};
+      own_it = -1;
       for (;;) {
+        // find a claimable run: the lanes look at 64 of this XCD's streams at
+        // once (lane l at stream s + l, so the stream this block last served
+        // comes first); one load per stream decides (batch.h).  Then lane 0
+        // claims from the candidates in lane order.
+        uint32_t sl = s;
+        for (uint32_t base = 0; base < ns && it.sid < 0; base += WAVE) {
+          const uint32_t j = base + lane;
+          uint32_t q = s + j;
+          q = q < ns ? q : q - ns;   // s < ns and j < ns below, so one wrap suffices
+          bool can = false;
+          if (j < ns) can = claimable(xload(&streams[(size_t)q * nxcd + xcc].claim));
+          unsigned long long m = __ballot(can);
+          while (m != 0ull) {
+            const int L = (int)__builtin_ctzll(m);
+            m &= m - 1ull;
+            const uint32_t qL = __builtin_amdgcn_readfirstlane(__shfl(q, L, WAVE));
+            BatchStream& st = streams[(size_t)qL * nxcd + xcc];
+            unsigned long long w = 0;
+            if (lane == 0) w = xadd(&st.claim, 1ull);
+            w = bcast64(w);
+            if (claimable(w)) {
+              it.sid = (int)((size_t)qL * nxcd + xcc);
+              sl = qL;
+              it.gen = (uint32_t)(w >> 32);
+              it.run = (uint32_t)w & 0xffffu;
+              it.pidx = pass_of(const_table(st), it.gen);
+              break;
+            }
+          }
+        }
+        if (it.sid >= 0) {
+          s = sl;
+          // acquire for the block: the stream's earlier passes are visible.
+          // A block whose last acquire already followed the completion of
+          // every pass before this one (another run of the same pass) skips
+          // it.  One wave is enough, and all that is affordable: the waves
+          // of a compute unit share the caches above the L2 and their
+          // accesses pass them in order, and with every wave of 16 blocks
+          // invalidating, the first load of a pass took 9 us.
+          if (it.sid != acq_sid || it.gen > acq_gen) {
+            block_acquire();
+            acq_sid = it.sid;
+            acq_gen = it.gen;
+          }
+          break;
+        }
+        // nothing to claim: leave once every stream has settled; the stall
+        // detector ends the launch with an error instead of waiting forever
         uint32_t settled = 0, prog = 0;
         int err = 0;
         if (lane == 0) {
@@ -167,49 +215,6 @@ __global__ __launch_bounds__(COOP_BLOCK) void batch_kernel(const BatchPass* __re
         prog = __builtin_amdgcn_readfirstlane(prog);
         err = __builtin_amdgcn_readfirstlane(err);
         if (settled >= ns || err) break;
-        // find a claimable run: the lanes look at 64 of this XCD's streams at
-        // once (lane l at stream s + l, so the stream this block last served
-        // comes first); a settled stream's claim word is closed, so one load
-        // per stream decides.  Then lane 0 claims from the candidates in
-        // lane order.
-        uint32_t sl = s;
-        for (uint32_t base = 0; base < ns && it.sid < 0; base += WAVE) {
-          const uint32_t j = base + lane;
-          uint32_t q = s + j;
-          q = q < ns ? q : q - ns;   // s < ns and j < ns below, so one wrap suffices
-          bool can = false;
-          if (j < ns) {
-            const BatchStream& stl = streams[(size_t)q * nxcd + xcc];
-            const unsigned long long w = xload(&stl.claim);
-            const int p = pass_of(stl, (uint32_t)(w >> 32));
-            can = p >= 0 && (uint32_t)w < (uint32_t)passes[p].n_runs;
-          }
-          unsigned long long m = __ballot(can);
-          while (m != 0ull) {
-            const int L = (int)__builtin_ctzll(m);
-            m &= m - 1ull;
-            const uint32_t qL = __builtin_amdgcn_readfirstlane(__shfl(q, L, WAVE));
-            BatchStream& st = streams[(size_t)qL * nxcd + xcc];
-            unsigned long long w = 0;
-            if (lane == 0) w = xadd(&st.claim, 1ull);
-            w = bcast64(w);
-            const int p = pass_of(st, (uint32_t)(w >> 32));
-            if (p >= 0 && (uint32_t)w < (uint32_t)passes[p].n_runs) {
-              it.sid = (int)((size_t)qL * nxcd + xcc);
-              sl = qL;
-              it.pidx = p;
-              it.run = (uint32_t)w;
-              it.gen = (uint32_t)(w >> 32);
-              break;
-            }
-          }
-        }
-        if (it.sid >= 0) {
-          s = sl;
-          break;
-        }
-        // nothing to claim: the stall detector ends the launch with an error
-        // instead of waiting forever
         const unsigned long long now = __builtin_amdgcn_s_memrealtime();
         if (prog != seen_progress) {
           seen_progress = prog;
@@ -218,7 +223,7 @@ __global__ __launch_bounds__(COOP_BLOCK) void batch_kernel(const BatchPass* __re
           if (lane == 0) xstore(&X.error, 1);
           break;
         }
-        __builtin_amdgcn_s_sleep(2);
+        __builtin_amdgcn_s_sleep(1);
       }
       if (lane == 0) item = it;
     }
@@ -228,109 +233,117 @@ __global__ __launch_bounds__(COOP_BLOCK) void batch_kernel(const BatchPass* __re
     const int pidx = __builtin_amdgcn_readfirstlane(item.pidx);
     const uint32_t run = __builtin_amdgcn_readfirstlane(item.run), gen = __builtin_amdgcn_readfirstlane(item.gen);
     BatchStream& st = streams[sid];
-    const BatchPass& B = passes[pidx];
+    const BatchStream& sc = const_table(st);   // for the fields no launch writes
+    const BatchPass& B = const_table(passes[pidx]);
     const VmParams& P = B.P;
     const uint32_t n_runs = (uint32_t)B.n_runs;
-    // acquire, in every wave: the stream's earlier passes are visible.  A
-    // block whose last acquire already followed the completion of every pass
-    // before this one (another run of the same pass, or the next pass after
-    // it finished the previous one) skips it.
-    if (sid != acq_sid || gen > acq_gen) {
-      xcd_acquire();
-      acq_sid = sid;
-      acq_gen = gen;
-    }
     const int64_t t_begin = (int64_t)run * P.tiles_per_wave;
     const int64_t t_end = min(t_begin + P.tiles_per_wave, P.n_tiles);
     for (int64_t t = t_begin; t < t_end; ++t) {
-      coop_tile<BT, BHV>(P, t, coop_dyn_lds, slots, staged, tot);
+      coop_tile<BT, BHV>(P, t, coop_dyn_lds, tot);
       if (P.n_red > 0) {
         // (lane 0 of wave k holds sum k; a one-tile pass keeps it in LDS)
-        if (P.n_tiles > 1 && wib < P.n_red && lane == 0) st.tsum[wib * st.tsum_stride + t] = tot[wib];
+        if (P.n_tiles > 1 && wib < P.n_red && lane == 0) global_ptr<double>(sc.tsum)[wib * sc.tsum_stride + t] = tot[wib];
         if (t + 1 < t_end) __syncthreads();   // the summands' LDS is written again
       }
     }
     since = __builtin_amdgcn_s_memrealtime();
-    // release every wave's stores of this run, then count it
-    xcd_release();
-    __syncthreads();
-    have = false;
     if (n_runs > 1) {
-      if (threadIdx.x == 0) last_run = xadd(&st.done, 1u) + 1 == n_runs ? 1u : 0u;
+      // release every wave's stores of this run, then count it
+      xcd_release();
       __syncthreads();
+      if (wib == 0) {
+        uint32_t d = 0;
+        if (lane == 0) d = xadd(&st.done, 1u);
+        const bool last = __builtin_amdgcn_readfirstlane(d) + 1 == n_runs;
+        if (last) block_acquire();   // the other runs' tile sums and outputs
+        if (lane == 0) last_run = last ? 1u : 0u;
+      }
+      __syncthreads();
+      have = false;
       if (!__builtin_amdgcn_readfirstlane(last_run)) continue;
-      // the other runs' tile sums and outputs (a one-run pass was all this
-      // block's)
-      xcd_acquire();
     }
     acq_sid = sid;
     acq_gen = gen + 1;
-    // ---- the last run of the pass: reductions, then advance the stream ------
+    // ---- the pass is complete: reductions, then advance the stream ------------
     if (P.n_red > 0) {
       if (P.n_tiles <= 4 * WAVE) {
         if (wib < P.n_red) {
-          const double v = P.n_tiles == 1 ? tot[wib] : block_tree(st.tsum + wib * st.tsum_stride, (int)P.n_tiles, lane);
+          const double v = P.n_tiles == 1 ? tot[wib] : block_tree(global_ptr<double>(sc.tsum) + wib * sc.tsum_stride, (int)P.n_tiles, lane);
           if (lane == 0) {
-            double* res = (double*)B.result[wib];
-            *res = B.init[wib] ? v : load_data_f64(res) + v;
+            double* res = global_ptr<double>(B.result[wib]);
+            *res = B.init[wib] ? v : load_0d<double>(res) + v;
           }
         }
       } else if (wib == 0) {
         // (the chunk sums' scratch is one per stream)
-        double* chunk = st.tsum + (int64_t)VM_MAXRED * st.tsum_stride;
+        double* tsum = global_ptr<double>(sc.tsum);
+        double* chunk = tsum + (int64_t)VM_MAXRED * sc.tsum_stride;
         for (int k = 0; k < P.n_red; ++k) {
-          const double v = wave_tree(st.tsum + k * st.tsum_stride, P.n_tiles, chunk, lane);
+          const double v = wave_tree(tsum + k * sc.tsum_stride, P.n_tiles, chunk, lane);
           if (lane == 0) {
-            double* res = (double*)B.result[k];
-            *res = B.init[k] ? v : load_data_f64(res) + v;
+            double* res = global_ptr<double>(B.result[k]);
+            *res = B.init[k] ? v : load_0d<double>(res) + v;
           }
         }
       }
-      xcd_release();
-      __syncthreads();
     }
+    __syncthreads();
     if (wib == 0) {
-      int32_t next_status = BS_RUNNING;
-      const uint32_t g1 = gen + 1;
-      if (st.n_body == 0) {
-        if ((int64_t)g1 >= st.n_pre) next_status = BS_DONE;
-      } else if ((int64_t)g1 > st.n_pre && ((g1 - (uint32_t)st.n_pre) % (uint32_t)st.n_body) == 0) {
+      int32_t status = BS_RUNNING;
+      const int body0 = sc.pass0 + sc.n_pre, end = body0 + sc.n_body;
+      int np = pidx + 1;
+      if (np == end && sc.n_body > 0) {
+        np = body0;
         // a repetition of the body is complete (only this block touches the
         // counters now: the stream's next pass is not yet published)
-        int32_t it = 0, rit = 0;
+        if (own_it < 0) {
+          own_it = __builtin_amdgcn_readfirstlane(xload(&st.iters));
+          own_rit = __builtin_amdgcn_readfirstlane(xload(&st.round_iters));
+        }
+        own_it += 1;
+        own_rit += 1;
         if (lane == 0) {
-          it = xload(&st.iters) + 1;
-          rit = xload(&st.round_iters) + 1;
-          xstore(&st.iters, it);
-          xstore(&st.round_iters, rit);
+          xstore(&st.iters, own_it);
+          xstore(&st.round_iters, own_rit);
         }
-        it = __builtin_amdgcn_readfirstlane(it);
-        rit = __builtin_amdgcn_readfirstlane(rit);
-        bool stop = it >= st.max_iter;
-        if (!stop && st.conv_a) {
-          const double a = load_data_f64(st.conv_a), b = load_data_f64(st.conv_b);
-          stop = a <= st.tol * b;
+        bool stop = own_it >= sc.max_iter;
+        if (!stop && sc.conv_a) {
+          const double a = load_0d<double>(sc.conv_a), b = load_0d<double>(sc.conv_b);
+          stop = a <= sc.tol * b;
         }
-        if (stop) next_status = BS_DONE;
-        else if (ctl->round_limit > 0 && rit >= ctl->round_limit) next_status = BS_PAUSED;
-      } else if (st.n_pre > 0 && (int64_t)g1 == st.n_pre && st.max_iter <= 0) {
-        next_status = BS_DONE;
+        if (stop) status = BS_DONE;
+        else if (ctl->round_limit > 0 && own_rit >= ctl->round_limit) status = BS_PAUSED;
+      } else if (np == body0 && (sc.n_body == 0 || sc.max_iter <= 0)) {
+        status = BS_DONE;
       }
+      if (status != BS_RUNNING) np = -1;
       if (lane == 0) {
-        xstore(&st.done, 0u);
-        if (next_status != BS_RUNNING) xstore(&st.status, next_status);
-        xcd_release();
-        // the next pass opens with its first run taken by this block
-        xstore(&st.claim, ((unsigned long long)g1 << 32) | (next_status != BS_RUNNING ? CLAIM_CLOSED : 1ull));
-        if (next_status != BS_RUNNING) xadd(&X.n_settled, 1u);
-        xadd(&X.progress, 1u);
-        item.pidx = next_status != BS_RUNNING ? -1 : pass_of(st, g1);
+        item.pidx = np;
         item.run = 0u;
-        item.gen = g1;
+        item.gen = gen + 1;
+        item.status = status;
+        // a next pass of one run is this block's alone: nothing to tell
+        // anyone, and no store has to be waited for
+        item.publish = np < 0 || const_table(passes[np]).n_runs > 1;
+        xadd(&X.progress, 1u);
       }
     }
     __syncthreads();
     have = __builtin_amdgcn_readfirstlane(item.pidx) >= 0;
+    if (__builtin_amdgcn_readfirstlane(item.publish)) {
+      xcd_release();   // every wave's stores since the stream was last published
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        const int32_t status = item.status, np = item.pidx;
+        xstore(&st.done, 0u);
+        if (status != BS_RUNNING) xstore(&st.status, status);
+        xcd_release();
+        // the next pass opens with its first run taken by this block
+        xstore(&st.claim, claim_word(item.gen, np < 0 ? 0u : (uint32_t)const_table(passes[np]).n_runs, 1u));
+        if (status != BS_RUNNING) xadd(&X.n_settled, 1u);
+      }
+    }
   }
 }
 

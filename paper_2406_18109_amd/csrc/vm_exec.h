@@ -684,8 +684,12 @@ __device__ __forceinline__ T tile_lane_sum(const T* ds, const int lane, const in
   }
   const bool all = __ballot(whole) == ~0ull;
   T acc = (T)0;
+  int rmax = rl[0];
+#pragma unroll
+  for (int v = 1; v < V; ++v) rmax = max(rmax, rl[v]);
 #pragma unroll 1
   for (int h = 0; h < RED_TH; h += H) {
+    if (__ballot(h < rmax) == 0ull) break;
     vecA w[H];
 #pragma unroll
     for (int r = 0; r < H; ++r) w[r] = *(const vecA*)(ds + (h + r) * TW + lane * V);
