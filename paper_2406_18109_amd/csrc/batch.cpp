@@ -128,7 +128,7 @@ int dfx_batch_create(int32_t device, void* stream, dfx_batch** out) {
   // one block of 16 waves per compute unit, every one resident; gfx950 has
   // 32 compute units per XCD, and blocks are dispatched to the XCDs in turn,
   // so each XCD gets grid / n_xcd of them
-  b->n_xcd = std::max(1, std::min(BATCH_MAX_XCD, n_cu / 32));
+  b->n_xcd = std::max(1, std::min(MAX_XCD, n_cu / 32));
   b->n_cu = n_cu;
   b->grid = std::max(b->n_xcd, n_cu);
   *out = b;
@@ -311,7 +311,7 @@ int dfx_batch_run(dfx_batch* b, int32_t round_limit, int32_t restart) {
   }
   const uint32_t lds = coop_lds(max_red, spmv);
   for (size_t i = 0; i < ns; ++i) {
-    BatchXcd& X = b->ctl.x[i % b->n_xcd];
+    XcdCtl& X = b->ctl.x[i % b->n_xcd];
     X.n_streams += 1;
     if (b->streams[i].status != BS_RUNNING) X.n_settled += 1;
   }

@@ -11,28 +11,14 @@
 // advances the stream.  No block waits for another: a block with nothing to
 // claim looks at the XCD's other streams.
 #pragma once
-#include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "claim.h"
 #include "vm.h"
 
 namespace dfx {
 
 constexpr int BATCH_MAX_RUNS = 4096;  // work items per pass (runs of tiles_per_wave tiles)
-
-// A stream's claim word: passes completed << 32 | runs of the current pass
-// << 16 | next run to claim, so that one load tells whether a run is left.
-// A settled (done or paused) stream has no runs.  Claimers add one after
-// seeing a run left, so the next-run field passes the runs by at most one
-// per block of the launch and never reaches the runs field.  While a block
-// keeps a stream to itself (passes of one run) the word stays that of the
-// last published pass, all of whose runs are taken.
-__host__ __device__ inline unsigned long long claim_word(uint32_t gen, uint32_t runs, uint32_t next) {
-  return (unsigned long long)gen << 32 | (unsigned long long)runs << 16 | next;
-}
-__host__ __device__ inline bool claimable(unsigned long long w) {
-  return ((uint32_t)w & 0xffffu) < ((uint32_t)w >> 16);
-}
 
 struct BatchPass {
   VmParams P;                    // red_partials unused: tile sums go to the stream's tsum
@@ -58,20 +44,9 @@ struct BatchStream {
   int32_t status;                // BatchStatus
 };
 
-// Streams are pinned to XCDs: stream s runs on the compute units of XCD
-// s % n_xcd, whose L2 is the coherence point of everything the stream's
-// waves exchange inside a launch.  Each XCD's counters sit in their own
-// 256-byte line.
-constexpr int BATCH_MAX_XCD = 8;
-struct BatchXcd {
-  uint32_t n_streams;            // streams of this XCD
-  uint32_t n_settled;            // of them, done or paused in this launch
-  uint32_t progress;             // passes completed: the stall detector's clock
-  int32_t error;                 // 1: the stall detector fired
-  uint32_t pad[60];
-};
+// Stream s runs on the compute units of XCD s % n_xcd.
 struct BatchCtl {
-  BatchXcd x[BATCH_MAX_XCD];
+  XcdCtl x[MAX_XCD];
   uint32_t n_streams, n_xcd;
   int32_t round_limit;           // > 0: a stream pauses after this many repetitions in one launch
   uint32_t xcc_seen;             // bit k: some wave ran on XCD k (diagnostics)

@@ -27,6 +27,7 @@
 #include "batch.h"
 #include "dev_common.h"
 #include "coop_exec.h"
+#include "worker.h"
 #include "vm_exec.h"
 
 namespace dfx {
@@ -38,41 +39,6 @@ namespace {
 // transcendental op set (HV 1) when any pass needs it, else the arithmetic
 // one (HV 0, two rows per step).
 typedef double BT;
-
-// Synchronisation.  Streams are pinned to XCDs, so every wave that reads a
-// stream's data runs on the XCD whose L2 holds it.  A run's stores are
-// released by waiting for their completion (s_waitcnt: they have reached
-// the L2), without writing the L2 back to memory as an agent-scope release
-// would; a claim or a completed count is followed by the agent-scope
-// acquire (it invalidates the CU's caches above the L2).  Control words are
-// agent-scope atomics.  A message-passing test between waves of one XCD on
-// MI355X (writer: plain stores, wait, flag; reader: flag, acquire, loads)
-// saw no stale value over 8 x 10^5 messages with this pair, and stale values
-// with an L1-only invalidate (buffer_inv sc0) as the acquire.
-__device__ __forceinline__ void xcd_release() {
-  __builtin_amdgcn_s_waitcnt(0);
-  asm volatile("" ::: "memory");
-}
-// By one wave, before a block barrier: for every wave of the block.
-__device__ __forceinline__ void block_acquire() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  __builtin_amdgcn_s_waitcnt(0);
-  asm volatile("" ::: "memory");
-}
-template <typename U> __device__ __forceinline__ U xload(U* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename U> __device__ __forceinline__ void xstore(U* p, U v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename U> __device__ __forceinline__ U xadd(U* p, U v) {
-  return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned long long bcast64(unsigned long long v) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return ((unsigned long long)hi << 32) | lo;
-}
 
 // Pass index (into the batch's pass table) of the g-th pass a stream runs;
 // -1 past the end of a stream without a repeated body.
@@ -105,13 +71,6 @@ __device__ double wave_tree(const double* a, int64_t n, double* scratch, int lan
   return __shfl(v, 0, WAVE);
 }
 
-// Stall detector: a wave that finds nothing to claim while no pass of its
-// XCD's streams has completed for this many ticks of the 100 MHz constant
-// clock (2 s) ends the launch with an error.
-#ifndef DFX_BATCH_STALL_TICKS
-#define DFX_BATCH_STALL_TICKS 200000000ull
-#endif
-
 // What wave 0 found, or decided, for its block.
 struct BatchItem {
   int32_t sid, pidx;   // sid < 0: leave; pidx < 0: nothing taken, search
@@ -138,7 +97,7 @@ __global__ __launch_bounds__(COOP_BLOCK) void batch_kernel(const BatchPass* __re
     __hip_atomic_fetch_add(&ctl->waves[xcc & 15], (uint32_t)COOP_WAVES, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   if (xcc >= nxcd) return;
-  BatchXcd& X = ctl->x[xcc];
+  XcdCtl& X = ctl->x[xcc];
   const uint32_t ns = X.n_streams;   // streams xcc, xcc + nxcd, ...
   if (ns == 0) return;
   // (wave 0 alone searches and decides; these are its own)
@@ -156,38 +115,14 @@ __global__ __launch_bounds__(COOP_BLOCK) void batch_kernel(const BatchPass* __re
       BatchItem it = {-1, -1, 0u, 0u, BS_RUNNING, 0};
       own_it = -1;
       for (;;) {
-        // find a claimable run: the lanes look at 64 of this XCD's streams at
-        // once (lane l at stream s + l, so the stream this block last served
-        // comes first); one load per stream decides (batch.h).  Then lane 0
-        // claims from the candidates in lane order.
-        uint32_t sl = s;
-        for (uint32_t base = 0; base < ns && it.sid < 0; base += WAVE) {
-          const uint32_t j = base + lane;
-          uint32_t q = s + j;
-          q = q < ns ? q : q - ns;   // s < ns and j < ns below, so one wrap suffices
-          bool can = false;
-          if (j < ns) can = claimable(xload(&streams[(size_t)q * nxcd + xcc].claim));
-          unsigned long long m = __ballot(can);
-          while (m != 0ull) {
-            const int L = (int)__builtin_ctzll(m);
-            m &= m - 1ull;
-            const uint32_t qL = __builtin_amdgcn_readfirstlane(__shfl(q, L, WAVE));
-            BatchStream& st = streams[(size_t)qL * nxcd + xcc];
-            unsigned long long w = 0;
-            if (lane == 0) w = xadd(&st.claim, 1ull);
-            w = bcast64(w);
-            if (claimable(w)) {
-              it.sid = (int)((size_t)qL * nxcd + xcc);
-              sl = qL;
-              it.gen = (uint32_t)(w >> 32);
-              it.run = (uint32_t)w & 0xffffu;
-              it.pidx = pass_of(const_table(st), it.gen);
-              break;
-            }
-          }
-        }
-        if (it.sid >= 0) {
-          s = sl;
+        unsigned long long w = 0;
+        const int q = find_run(s, ns, [&](uint32_t k) { return &streams[(size_t)k * nxcd + xcc].claim; }, w);
+        if (q >= 0) {
+          s = (uint32_t)q;
+          it.sid = (int)((size_t)q * nxcd + xcc);
+          it.gen = (uint32_t)(w >> 32);
+          it.run = (uint32_t)w & 0xffffu;
+          it.pidx = pass_of(const_table(streams[it.sid]), it.gen);
           // acquire for the block: the stream's earlier passes are visible.
           // A block whose last acquire already followed the completion of
           // every pass before this one (another run of the same pass) skips
@@ -202,28 +137,7 @@ __global__ __launch_bounds__(COOP_BLOCK) void batch_kernel(const BatchPass* __re
           }
           break;
         }
-        // nothing to claim: leave once every stream has settled; the stall
-        // detector ends the launch with an error instead of waiting forever
-        uint32_t settled = 0, prog = 0;
-        int err = 0;
-        if (lane == 0) {
-          settled = xload(&X.n_settled);
-          prog = xload(&X.progress);
-          err = xload(&X.error);
-        }
-        settled = __builtin_amdgcn_readfirstlane(settled);
-        prog = __builtin_amdgcn_readfirstlane(prog);
-        err = __builtin_amdgcn_readfirstlane(err);
-        if (settled >= ns || err) break;
-        const unsigned long long now = __builtin_amdgcn_s_memrealtime();
-        if (prog != seen_progress) {
-          seen_progress = prog;
-          since = now;
-        } else if (now - since > DFX_BATCH_STALL_TICKS) {
-          if (lane == 0) xstore(&X.error, 1);
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
+        if (idle(X, seen_progress, since)) break;
       }
       if (lane == 0) item = it;
     }

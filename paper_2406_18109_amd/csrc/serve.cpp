@@ -3,8 +3,9 @@
 // A scheduler thread owns a HIP stream and a set of device slots.  Each round
 // it admits queued solves while a slot is free and their HBM footprint fits
 // the budget (matrix and right-hand side copied in, state initialised on
-// device), launches the four CG phases once for all resident solves (work
-// items = (solve, canonical tile)), reads back the per-solve status words and
+// device), runs several CG iterations of all resident solves (work items =
+// (solve, canonical tile), in one persistent launch or, with very large
+// solves, as phase launches), reads back the per-solve status words and
 // retires converged solves (x copied out, memory returned).  Requests that
 // arrive while others run join at the next round, so their work overlaps on
 // the device.  Every solve's arithmetic depends only on its own data and the
@@ -15,6 +16,7 @@
 #include <atomic>
 #include <chrono>
 #include <cmath>
+#include <cstdlib>
 #include <condition_variable>
 #include <cstring>
 #include <deque>
@@ -27,6 +29,8 @@
 namespace dfx {
 
 int launch_serve_phase(const ServeLaunch& L, hipStream_t stream);
+int launch_serve_round(SolveDev* solves, ServeClaim* claims, const int32_t* list, ServeRound* ctl, int grid,
+                       hipStream_t stream);
 
 static double wall_now() {
   return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
@@ -112,6 +116,9 @@ struct Server {
   int32_t* d_fin = nullptr;         // [new solves | all resident solves], max_slots each
   int32_t* h_fin = nullptr;         // pinned staging
   int n_fresh = 0, n_used = 0;
+  char* d_round = nullptr;          // [ServeRound | ServeClaim x max_slots | list x max_slots]
+  char* h_round = nullptr;          // pinned staging; its ServeRound is read back
+  int n_cu = 0;
   size_t item_cap = 0;
   Tuner tuner;
   dfx_serve_counters stats{};
@@ -166,6 +173,7 @@ static bool admit_one(Server& S, ServeReq& q, int slot) {
   d.q = (double*)take(n * 8);
   d.partials = (double*)take(tiles_of(n) * 8);
   d.n = n;
+  d.nnz = (int32_t)nnz;
   d.n_tiles = (int32_t)tiles_of(n);
   d.max_iter = S.cfg.max_iter;
   d.tol = S.cfg.tol;
@@ -220,6 +228,103 @@ static int run_phase(Server& S, int phase, int64_t n_items, int64_t off) {
   return 0;
 }
 
+// The round as phase launches over the work items (solve, tile).
+static int phase_round(Server& S, int ipr, size_t n_all, size_t n_new) {
+  size_t k = 0;
+  for (size_t i = 0; i < S.slots.size(); ++i)
+    if (S.slots[i].used && S.slots[i].fresh)
+      for (int t = 0; t < S.slots[i].n_tiles; ++t) { S.h_items[k] = (int32_t)i; S.h_items[S.item_cap + k] = t; ++k; }
+  for (size_t i = 0; i < S.slots.size(); ++i)
+    if (S.slots[i].used)
+      for (int t = 0; t < S.slots[i].n_tiles; ++t) { S.h_items[k] = (int32_t)i; S.h_items[S.item_cap + k] = t; ++k; }
+  const size_t ms = S.slots.size();
+  S.n_fresh = S.n_used = 0;
+  for (size_t i = 0; i < ms; ++i) {
+    if (!S.slots[i].used) continue;
+    if (S.slots[i].fresh) S.h_fin[S.n_fresh++] = (int32_t)i;
+    S.h_fin[ms + S.n_used++] = (int32_t)i;
+  }
+  bool ok = hipMemcpyAsync(S.d_items, S.h_items, k * sizeof(int32_t), hipMemcpyHostToDevice, S.stream) == hipSuccess &&
+            hipMemcpyAsync(S.d_items + S.item_cap, S.h_items + S.item_cap, k * sizeof(int32_t),
+                           hipMemcpyHostToDevice, S.stream) == hipSuccess &&
+            hipMemcpyAsync(S.d_fin, S.h_fin, 2 * ms * sizeof(int32_t), hipMemcpyHostToDevice, S.stream) == hipSuccess;
+  int e = ok ? 0 : 1;
+  if (!e) e = run_phase(S, PH_INIT, (int64_t)n_new, 0);
+  for (int j = 0; j < ipr && !e; ++j) {
+    e = run_phase(S, PH_SPMV_DOT, (int64_t)n_all, (int64_t)n_new);
+    if (!e) e = run_phase(S, PH_AXPY_DOT, (int64_t)n_all, (int64_t)n_new);
+    if (!e) e = run_phase(S, PH_UPDATE_P, (int64_t)n_all, (int64_t)n_new);
+  }
+  return e;
+}
+
+// The resident solves spread over the XCDs, largest first, each to the XCD
+// with the fewest tiles so far (a solve's result does not depend on where it
+// runs).  Returns the tiles of the fullest XCD.
+static int64_t spread(const Server& S, std::vector<int> (&at)[MAX_XCD]) {
+  const int n_xcd = std::max(1, std::min(MAX_XCD, S.n_cu / 32));
+  std::vector<int> order;
+  for (size_t i = 0; i < S.slots.size(); ++i)
+    if (S.slots[i].used) order.push_back((int)i);
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return S.slots[a].n_tiles > S.slots[b].n_tiles; });
+  int64_t load[MAX_XCD] = {};
+  for (int i : order) {
+    int x = 0;
+    for (int k = 1; k < n_xcd; ++k)
+      if (load[k] < load[x]) x = k;
+    load[x] += S.slots[i].n_tiles;
+    at[x].push_back(i);
+  }
+  return *std::max_element(load, load + n_xcd);
+}
+
+// Whether the round runs as one persistent launch: the fullest XCD has at
+// most this many tiles.  There a phase is bound by latency, and costs less
+// than the phase launches; with more, those use the chip's bandwidth better.
+// Measured, an iteration persistent against phases: one solve of side 256
+// (16 tiles) 32 against 104 us, 512 (64) 71 against 109, 724 (128) 133
+// against 128, 1024 (256) 252 against 134; sixteen solves of side 256 (32
+// tiles an XCD) 78 against 155, of side 512 (128) 241 against 243.
+// DFX_SERVE_ROUND=0 or 1 forces one of the two.
+constexpr int64_t ROUND_MAX_TILES = 128;
+static bool round_fits(int64_t fullest) {
+  const char* e = std::getenv("DFX_SERVE_ROUND");
+  if (e && (e[0] == '0' || e[0] == '1')) return e[0] == '1';
+  return fullest <= ROUND_MAX_TILES;
+}
+
+// The round as one persistent launch.
+static int persistent_round(Server& S, int ipr, const std::vector<int> (&at)[MAX_XCD]) {
+  const size_t ms = S.slots.size();
+  ServeRound* R = (ServeRound*)S.h_round;
+  ServeClaim* claims = (ServeClaim*)(S.h_round + sizeof(ServeRound));
+  int32_t* list = (int32_t*)(S.h_round + sizeof(ServeRound) + ms * sizeof(ServeClaim));
+  std::memset(R, 0, sizeof(ServeRound));
+  R->n_xcd = (uint32_t)std::max(1, std::min(MAX_XCD, S.n_cu / 32));
+  R->iters = ipr;
+  int n = 0;
+  for (uint32_t x = 0; x < R->n_xcd; ++x) {
+    R->x[x].first = (uint32_t)n;
+    R->x[x].n_streams = (uint32_t)at[x].size();
+    for (int i : at[x]) {
+      const ServeSlot& sl = S.slots[i];
+      claims[i].claim = claim_word(sl.fresh ? PH_INIT : PH_SPMV_DOT, (uint32_t)sl.n_tiles, 0);
+      claims[i].done = 0;
+      claims[i].round_iters = 0;
+      list[n++] = i;
+    }
+  }
+  const size_t bytes = sizeof(ServeRound) + ms * (sizeof(ServeClaim) + sizeof(int32_t));
+  int e = hipMemcpyAsync(S.d_round, S.h_round, bytes, hipMemcpyHostToDevice, S.stream);
+  if (!e)
+    e = launch_serve_round(S.d_solves, (ServeClaim*)(S.d_round + sizeof(ServeRound)),
+                           (const int32_t*)(S.d_round + sizeof(ServeRound) + ms * sizeof(ServeClaim)),
+                           (ServeRound*)S.d_round, std::max(1, S.n_cu), S.stream);
+  if (!e) e = hipMemcpyAsync(S.h_round, S.d_round, sizeof(ServeRound), hipMemcpyDeviceToHost, S.stream);
+  S.stats.launches += 1;
+  return e;
+}
+
 static void scheduler(Server* Sp) {
   Server& S = *Sp;
   (void)hipSetDevice(S.device);
@@ -255,41 +360,27 @@ static void scheduler(Server* Sp) {
       }
     }
     // ---- one round: init new solves, then the three CG phases for all -------
-    size_t n_all = 0, n_new = 0;
-    for (auto& sl : S.slots)
-      if (sl.used) { n_all += sl.n_tiles; if (sl.fresh) n_new += sl.n_tiles; }
-    if (!grow_items(S, n_all + n_new)) { std::lock_guard<std::mutex> lk(S.mu); fail_locked(S, "work list allocation failed"); break; }
-    size_t k = 0;
-    for (size_t i = 0; i < S.slots.size(); ++i)
-      if (S.slots[i].used && S.slots[i].fresh)
-        for (int t = 0; t < S.slots[i].n_tiles; ++t) { S.h_items[k] = (int32_t)i; S.h_items[S.item_cap + k] = t; ++k; }
-    for (size_t i = 0; i < S.slots.size(); ++i)
-      if (S.slots[i].used)
-        for (int t = 0; t < S.slots[i].n_tiles; ++t) { S.h_items[k] = (int32_t)i; S.h_items[S.item_cap + k] = t; ++k; }
-    const size_t ms = S.slots.size();
-    S.n_fresh = S.n_used = 0;
-    for (size_t i = 0; i < ms; ++i) {
-      if (!S.slots[i].used) continue;
-      if (S.slots[i].fresh) S.h_fin[S.n_fresh++] = (int32_t)i;
-      S.h_fin[ms + S.n_used++] = (int32_t)i;
-    }
-    bool ok = hipMemcpyAsync(S.d_items, S.h_items, k * sizeof(int32_t), hipMemcpyHostToDevice, S.stream) == hipSuccess &&
-              hipMemcpyAsync(S.d_items + S.item_cap, S.h_items + S.item_cap, k * sizeof(int32_t),
-                             hipMemcpyHostToDevice, S.stream) == hipSuccess &&
-              hipMemcpyAsync(S.d_fin, S.h_fin, 2 * ms * sizeof(int32_t), hipMemcpyHostToDevice, S.stream) == hipSuccess;
-    int e = ok ? 0 : 1;
-    if (!e) e = run_phase(S, PH_INIT, (int64_t)n_new, 0);
     // several iterations per round amortise the host round trip; a solve that
     // converges inside the round is skipped by the remaining phases
     const int ipr = S.cfg.iters_per_round > 0 ? S.cfg.iters_per_round : 8;
-    for (int j = 0; j < ipr && !e; ++j) {
-      e = run_phase(S, PH_SPMV_DOT, (int64_t)n_all, (int64_t)n_new);
-      if (!e) e = run_phase(S, PH_AXPY_DOT, (int64_t)n_all, (int64_t)n_new);
-      if (!e) e = run_phase(S, PH_UPDATE_P, (int64_t)n_all, (int64_t)n_new);
+    size_t n_all = 0, n_new = 0;
+    for (auto& sl : S.slots)
+      if (sl.used) { n_all += sl.n_tiles; if (sl.fresh) n_new += sl.n_tiles; }
+    std::vector<int> at[MAX_XCD];
+    const bool persistent = round_fits(spread(S, at));
+    int e;
+    if (persistent) {
+      e = persistent_round(S, ipr, at);
+    } else {
+      if (!grow_items(S, n_all + n_new)) { std::lock_guard<std::mutex> lk(S.mu); fail_locked(S, "work list allocation failed"); break; }
+      e = phase_round(S, ipr, n_all, n_new);
     }
     // one transfer of every slot's state (unused slots are ignored below)
     if (!e) e = hipMemcpyAsync(S.h_solves, S.d_solves, sizeof(SolveDev) * S.slots.size(), hipMemcpyDeviceToHost, S.stream);
     if (!e) e = hipStreamSynchronize(S.stream);
+    if (!e && persistent)
+      for (const XcdCtl& x : ((const ServeRound*)S.h_round)->x)
+        if (x.error) e = hipErrorLaunchTimeOut;   // (the stall detector ended the launch)
     if (e) { std::lock_guard<std::mutex> lk(S.mu); fail_locked(S, "round failed: " + std::string(hipGetErrorString((hipError_t)e))); break; }
     {
       // the admission copies have completed: the host arrays are free again
@@ -350,18 +441,24 @@ int dfx_serve_start(dfx_ctx* c, const dfx_serve_cfg* cfg) {
   S->cfg = *cfg;
   S->device = c->cfg.device;
   S->slots.resize(cfg->max_slots);
+  const size_t round_bytes = sizeof(ServeRound) + (size_t)cfg->max_slots * (sizeof(ServeClaim) + sizeof(int32_t));
   bool ok = hipSetDevice(S->device) == hipSuccess &&
             hipStreamCreateWithFlags(&S->stream, hipStreamNonBlocking) == hipSuccess &&
             hipMalloc((void**)&S->d_solves, sizeof(SolveDev) * cfg->max_slots) == hipSuccess &&
             hipHostMalloc((void**)&S->h_solves, sizeof(SolveDev) * cfg->max_slots, hipHostMallocDefault) == hipSuccess &&
             hipMalloc((void**)&S->d_fin, sizeof(int32_t) * 2 * cfg->max_slots) == hipSuccess &&
             hipHostMalloc((void**)&S->h_fin, sizeof(int32_t) * 2 * cfg->max_slots, hipHostMallocDefault) == hipSuccess &&
+            hipMalloc((void**)&S->d_round, round_bytes) == hipSuccess &&
+            hipHostMalloc((void**)&S->h_round, round_bytes, hipHostMallocDefault) == hipSuccess &&
+            hipDeviceGetAttribute(&S->n_cu, hipDeviceAttributeMultiprocessorCount, S->device) == hipSuccess &&
             hipEventCreate(&S->ev0) == hipSuccess && hipEventCreate(&S->ev1) == hipSuccess;
   if (!ok) {
     if (S->d_solves) (void)hipFree(S->d_solves);
     if (S->h_solves) (void)hipHostFree(S->h_solves);
     if (S->d_fin) (void)hipFree(S->d_fin);
     if (S->h_fin) (void)hipHostFree(S->h_fin);
+    if (S->d_round) (void)hipFree(S->d_round);
+    if (S->h_round) (void)hipHostFree(S->h_round);
     if (S->ev0) (void)hipEventDestroy(S->ev0);
     if (S->ev1) (void)hipEventDestroy(S->ev1);
     if (S->stream) (void)hipStreamDestroy(S->stream);
@@ -502,6 +599,8 @@ int dfx_serve_stop(dfx_ctx* c) {
   (void)hipHostFree(S->h_solves);
   if (S->d_fin) (void)hipFree(S->d_fin);
   if (S->h_fin) (void)hipHostFree(S->h_fin);
+  (void)hipFree(S->d_round);
+  (void)hipHostFree(S->h_round);
   (void)hipEventDestroy(S->ev0);
   (void)hipEventDestroy(S->ev1);
   (void)hipStreamDestroy(S->stream);

@@ -2,6 +2,8 @@
 #pragma once
 #include <stdint.h>
 
+#include "claim.h"
+
 namespace dfx {
 
 // One resident solve.  Vectors follow the canonical 1-D tiling of the
@@ -18,6 +20,7 @@ struct SolveDev {
   double* q;
   double* partials;     // n_tiles tile sums
   int64_t n;
+  int32_t nnz;
   int32_t n_tiles;
   int32_t max_iter;
   double tol;
@@ -49,6 +52,20 @@ struct ServeLaunch {
   int32_t grid;
   const int32_t* fin_slots;  // the solves of this phase, one block each in the scalar update
   int32_t n_fin;
+};
+
+// A round as one persistent launch (serve_round_kernel): every listed solve
+// runs up to `iters` iterations, its phases claimed tile by tile by the
+// blocks of the XCD it is pinned to for the round.
+struct ServeClaim {
+  unsigned long long claim;  // claim_word; the generation counts the solve's phases: 4 * iteration + phase
+  uint32_t done;             // tiles finished of the current phase
+  int32_t round_iters;       // iterations completed in this launch
+};
+struct ServeRound {
+  XcdCtl x[MAX_XCD];         // n_streams listed solves from `first` on
+  uint32_t n_xcd;
+  int32_t iters;
 };
 
 }  // namespace dfx
