@@ -36,7 +36,8 @@ template <int W, typename T> __device__ __forceinline__ T half_sum(T v) {
     return __builtin_bit_cast(T, ((uint64_t)hi[0] << 32) | lo[0]) + __builtin_bit_cast(T, ((uint64_t)hi[1] << 32) | lo[1]);
   } else {
     const u2 r = swap(__builtin_bit_cast(uint32_t, v));
-    return __builtin_bit_cast(T, r[0]) + __builtin_bit_cast(T, r[1]);
+    const uint32_t a = r[0], b = r[1];   // (a bit cast of a vector's element takes element 0)
+    return __builtin_bit_cast(T, a) + __builtin_bit_cast(T, b);
   }
 }
 
