@@ -1310,16 +1310,22 @@ static bool stencil_enabled() {
   return on;
 }
 
-// Whether a compiled pass runs each tile on a block of four waves
-// (red_split): one reduction, one tile per wave, no staging or row split,
-// and either a lone tile or more tiles than one block holds (so that the
-// block-sum launch is needed either way) up to RED_SPLIT_MAX_TILES.
+// Whether a compiled pass can run each tile on a block of four waves
+// (red_split): one reduction and either a lone tile or more tiles than one
+// block holds (so that the block-sum launch is needed either way) up to
+// RED_SPLIT_MAX_TILES.
+static bool red_split_tiles(const PassPlan& p) {
+  return p.red_cstore.size() == 1 && p.kind != 2 &&
+         (p.n_tiles == 1 || (p.n_tiles > 4 && p.n_tiles <= RED_SPLIT_MAX_TILES));
+}
+
+// Whether it does: one tile per wave, no staging or row split.
 // DFX_RED_SPLIT=0 turns it off.
 static bool red_split_ok(const PassPlan& p, const VmParams& P) {
   const char* e = std::getenv("DFX_RED_SPLIT");
   if (e && e[0] == '0') return false;
-  return P.n_red == 1 && P.st_n == 0 && P.row_split <= 1 && p.tiles_per_wave == 1 && p.kind != 2 &&
-         (p.n_tiles == 1 || (p.n_tiles > 4 && p.n_tiles <= RED_SPLIT_MAX_TILES)) && block_sum_slots(p) >= (size_t)p.n_tiles;
+  return red_split_tiles(p) && P.st_n == 0 && P.row_split <= 1 && p.tiles_per_wave == 1 &&
+         block_sum_slots(p) >= (size_t)p.n_tiles;
 }
 
 // A reducing pass whose tiles all belong to block 0 (one block sum) writes
@@ -1409,6 +1415,20 @@ static int realign_for(const PassPlan& p, const VmParams& P, size_t es, std::vec
   return any ? (int)m : 0;
 }
 
+// Dynamic LDS that a realigning pass's launch asks for and does not use: with
+// it four blocks fit a compute unit.  Such a pass holds few registers and
+// would have eight waves per SIMD resident, whose rows in flight are spread
+// over more of memory than streams well (four sweeps of an 8192^2 Jacobi
+// grid, with its copy at eight waves 2117 us, six 2087, four 2072, three
+// 2085).
+constexpr size_t REALIGN_LDS = 39 * 1024;
+// The same for a compiled stencil-staged pass: two blocks, so that eight
+// waves stream beside one another, not the twelve its buffers would allow
+// (four sweeps of an 8192^2 grid 2060 against 2117 us, of a 4099^2 one 610
+// against 614).  The interpreted one needs all the waves it can hold (2267
+// against 2664 us).
+constexpr size_t STENCIL_LDS = 50 * 1024;
+
 // Waves per tile of a pass without reductions (a power of two up to 32).
 // With one wave per tile a pass of few tiles leaves most of the chip idle
 // and each wave walks its tile's 32 rows in sequence (the 256-tile passes
@@ -1436,6 +1456,23 @@ static int row_split_for(const PassPlan& p, const VmParams& P) {
   return s;
 }
 
+// The vector modes need rows of at least one vector (the kernel's edge_shift).
+static bool edge_ok(const PassPlan& p) {
+  const int64_t V = p.dtype == DFX_F64 ? Lanes<double>::V : Lanes<float>::V;
+  return (p.is1d ? p.n1d : p.cols) >= V;
+}
+
+// Whether the pass's steps take the vector modes when it runs compiled:
+// outputs of column stride 1, inputs of column stride 1 or, over a 2-D
+// space, 0 (a value per row, a compile-time property of its stream).
+static int lin_cols(const PassPlan& p) {
+  for (auto& s : p.outs)
+    if (s.s_col != 1) return 0;
+  for (auto& s : p.ins)
+    if (s.s_col != 1 && !(s.s_col == 0 && !p.is1d)) return 0;
+  return 1;
+}
+
 // Passes that run compiled when jit is on (measured on MI355X):
 // transcendental passes, where the interpreter's dispatch dominates
 // (Black-Scholes FP64 over 2^26 options: 0.79 against 1.05 ms); small
@@ -1443,7 +1480,9 @@ static int row_split_for(const PassPlan& p, const VmParams& P) {
 // against 0.100 ms per iteration; the GMG 1023^2 iteration, whose fine-level
 // passes have 256 tiles: 0.82 ms with them compiled against 0.97 ms with the
 // limit at 256; 4096 gave 0.82 ms as well); stencil-staged passes (the 8192^2 Jacobi
-// sweep: 0.46 against 0.51 ms).  Large arithmetic and staged-SpMV passes
+// sweep: 0.46 against 0.51 ms); passes with a value broadcast along each row
+// (a table of 50021 x 1001 FP32 scaled per column and row: 129 instead of
+// 354 us, its accesses being element by element in the interpreter).  Large arithmetic and staged-SpMV passes
 // stream at the interpreter's rate or slightly below it compiled (the CG
 // 256^3 SpMV + dot: 438 against 390 us) and stay interpreted.
 // DFX_JIT_ALL=1 compiles every pass.
@@ -1452,7 +1491,7 @@ static bool jit_wanted(const PassPlan& p, int st_n) {
   if (all && all[0] == '1') return true;
   int64_t small = 1024;
   if (const char* e = std::getenv("DFX_JIT_SMALL")) small = std::atoll(e);
-  return p.tier != TIER_ARITH || p.n_tiles < small || st_n > 0;
+  return p.tier != TIER_ARITH || p.n_tiles < small || st_n > 0 || (lin_cols(p) && !p.unit_cols);
 }
 
 // The pass's program and kernel variant for compilation (rows: the rows per
@@ -1461,7 +1500,15 @@ static std::shared_ptr<JitEntry> request_compiled(PassPlan& p, int st_n, int row
   JitProgram g;
   g.n_in = (int)p.ins.size();
   g.n_out = (int)p.outs.size();
+  g.n_red = (int)p.red_cstore.size();
+  // (a stencil-staged kernel keeps the code it cannot reach: without it the
+  // compiler takes 163 registers instead of 120 for the Jacobi update, and
+  // four sweeps of a 4099^2 grid 622 instead of 615 us)
+  g.rsplit = st_n > 0 || red_split_tiles(p);
+  g.fin = st_n > 0 || p.n_tiles <= 4 * p.tiles_per_wave;   // one block
   for (int8_t d : p.realign) g.realign.push_back(d);
+  if (lin_cols(p))
+    for (auto& st : p.ins) g.bcol.push_back(st.s_col == 0);
   g.code = p.code;
   g.out_reg = p.out_reg;
   g.bc_reg = p.bc_reg;
@@ -1586,10 +1633,7 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
   P.spmv = p.kind == 1;
   P.grid = p.grid;
   P.unit_cols = p.unit_cols;
-  {
-    const int64_t V = p.dtype == DFX_F64 ? Lanes<double>::V : Lanes<float>::V;
-    P.vec_cols = p.unit_cols && (p.is1d ? (p.n1d % V == 0) : (p.cols % V == 0));
-  }
+  P.lin_cols = p.unit_cols && edge_ok(p);
   P.rows = p.rows;
   P.cols = p.cols;
   P.n1d = p.n1d;
@@ -1684,6 +1728,7 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
       if (jit_wanted(p, P.st_n) || ra_shift > 0) p.jit = request_compiled(p, P.st_n, rows, c.cfg.jit == 2);
     }
     if (p.jit && ra == p.realign) fn = jit_function(*p.jit, c.cfg.device, !c.capturing);
+    if (fn) P.lin_cols = lin_cols(p) && edge_ok(p);
   }
   // column shift (aligned output vectors), then row split, of passes
   // without reductions; either changes the launch shape only
@@ -1692,7 +1737,6 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
     const int64_t TWp = p.dtype == DFX_F64 ? Lanes<double>::TW : Lanes<float>::TW;
     const int64_t row_tiles = p.n_tiles / std::max<int64_t>(1, p.strips);
     P.col_shift = cs;
-    P.vec_cols = 0;
     P.strips = (p.cols + cs + TWp - 1) / TWp;
     P.n_tiles = row_tiles * P.strips;
     P.grid = grid_for((P.n_tiles + p.tiles_per_wave - 1) / p.tiles_per_wave);
@@ -1745,7 +1789,7 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
   if (c.fin_pending) {
     const char* fa = std::getenv("DFX_FIN_ATTACH");
     const bool fin_attach = !(fa && fa[0] == '0');
-    if (fin_attach && fn && P.grid == 1 && c.fin_f64 == (p.dtype == DFX_F64 ? 1 : 0) &&
+    if (fin_attach && fn && P.grid == 1 && p.n_tiles <= 4 * p.tiles_per_wave && c.fin_f64 == (p.dtype == DFX_F64 ? 1 : 0) &&
         c.fin.nblocks <= FIN_MAX_CHUNKS * FINAL_CHUNK) {
       P.fin = c.fin;
       c.fin_pending = false;
@@ -1759,9 +1803,11 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
   if (e != 0) {
   } else if (fn) {
     const JitVariant v = jit_variant(p.dtype == DFX_F64, p.tier, P.n_in, P.spmv, P.st_n, rows);
+    size_t lds = vm_dyn_lds_bytes(P, v.sten != 0);
+    if (ra_shift > 0) lds = std::max(lds, REALIGN_LDS);
+    if (v.sten) lds = std::max(lds, STENCIL_LDS);
     void* args[] = {(void*)&P};
-    e = (int)hipModuleLaunchKernel(fn, (unsigned)P.grid, 1, 1, BLOCK, 1, 1, (unsigned)vm_dyn_lds_bytes(P, v.sten != 0),
-                                   c.stream, args, nullptr);
+    e = (int)hipModuleLaunchKernel(fn, (unsigned)P.grid, 1, 1, BLOCK, 1, 1, (unsigned)lds, c.stream, args, nullptr);
     c.stats.compiled_launches += 1;
     if (c.capturing) c.capture_compiled += 1;
   } else {

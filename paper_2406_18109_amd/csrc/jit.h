@@ -45,9 +45,13 @@ struct JitVariant {
 // A pass's program: its instructions and register maps.
 struct JitProgram {
   int n_in = 0, n_out = 0;   // input and output streams
+  int n_red = 0;             // reductions
+  bool rsplit = false;       // may run under red_split
+  bool fin = false;          // may be one block that reduces an earlier pass's block sums
   std::vector<VmInstr> code;
   std::vector<int32_t> out_reg, bc_reg;
   std::vector<int32_t> st_on, st_dr, st_dc;   // stencil staging map (empty: none)
+  std::vector<int32_t> bcol;      // per input: 1 when its column stride is 0 (empty: none)
   std::vector<int32_t> realign;   // per input: elements past alignment after the strip shift (empty: none)
 };
 

@@ -138,7 +138,8 @@ struct VmParams {
   int32_t spmv;         // 1: row result of y = A x lands in VM_SPMV_REG first
   int32_t grid;         // blocks launched
   int32_t unit_cols;    // every stream has column stride 1 (padding slots 0)
-  int32_t vec_cols;     // unit_cols and the row width is a multiple of V
+  int32_t lin_cols;     // steps take the vector modes: unit_cols, or a compiled pass whose other
+                        // inputs have column stride 0 (a value per row)
   int64_t rows, cols;   // 2-D space; for 1-D: rows = ceil(n1d / TW), cols = TW
   int64_t n1d;
   int64_t n_tiles, strips;  // tiles, tiles per tile-row

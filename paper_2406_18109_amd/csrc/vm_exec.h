@@ -187,13 +187,55 @@ struct VmInterp {
   // some do
   static constexpr bool REALIGN = false;
   static constexpr int realign[VM_MAXIN] = {};
+  static constexpr int bcol[VM_MAXIN] = {};   // (compiled passes) input a has column stride 0
+  // (compiled passes) the pass's reductions, whether it may run under
+  // red_split and whether it may be one block that reduces an earlier pass's
+  // block sums.  What a pass cannot do is left out of its kernel: code that
+  // is never run still costs (the ordered sum of red_split in the kernel of
+  // a pass without reductions made 5e7 FP32 options 227 instead of 216 us).
+  static constexpr int N_RED = 0;
+  static constexpr bool RSPLIT = false, FIN = false;
   template <typename T, int HV, int NR, int NG, int GS, int E>
   static __device__ __forceinline__ void run(typename GVec<T, GS>::type (&)[NR], typename GVec<T, GS>::type (&)[NR],
                                              typename GVec<T, GS>::type (&)[NR], typename GVec<T, GS>::type (&)[NR],
                                              VmState<T, NG, GS>&, unsigned) {}
 };
 
-enum StepMode { MODE_FAST = 0, MODE_CLAMP = 1, MODE_SLOW = 2 };
+enum StepMode { MODE_FAST = 0, MODE_EDGE = 1, MODE_SLOW = 2 };
+
+// The valid elements of row u of a step.
+template <int V> __device__ __forceinline__ unsigned row_mask(const unsigned vmask, const int u) {
+  return (vmask >> (u * V)) & ((1u << V) - 1);
+}
+// Whether some lane of the step has a row of which only part is valid.
+template <int V, int U> __device__ __forceinline__ bool split_lane(const unsigned vmask) {
+  bool s = false;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const unsigned m = row_mask<V>(vmask, u);
+    s = s || (m != 0 && m != (1u << V) - 1);
+  }
+  return __ballot(s) != 0ull;
+}
+// Such a lane loads the vector that ends (or, across the space's left edge,
+// begins) at the boundary, so every edge step is one round of vector loads
+// like any other: edge_shift is that vector's offset from the lane's own
+// (valid elements m), edge_elem the lane's element v of it.  Rows are at
+// least V elements wide, so the vector stays inside the row.
+template <int V> __device__ __forceinline__ int edge_shift(const unsigned m) {
+  const int out = V - (int)__builtin_popcount(m);
+  return m == 0 ? 0 : (m & 1) ? -out : out;
+}
+template <typename T, int V, typename VA>
+__device__ __forceinline__ T edge_elem(const VA& w, const int sh, const int v) {
+  T x = w[v];
+#pragma unroll
+  for (int k = 1; k < V; ++k) {
+    if (v + k < V) x = sh == -k ? w[v + k] : x;
+    if (v - k >= 0) x = sh == k ? w[v - k] : x;
+  }
+  return x;
+}
 
 // y = A x for the V*64 elements of a step starting at element `base`.  The
 // row of element base + 64m + l is computed by lane l (consecutive rows on
@@ -294,7 +336,7 @@ template <class PG> __device__ __forceinline__ int n_out_of(const VmParams& P) {
   return PG::COMPILED ? PG::N_OUT : P.n_out;
 }
 
-// Vector-mode loads of one step (MODE_FAST or MODE_CLAMP) into L: every
+// Vector-mode loads of one step (MODE_FAST or MODE_EDGE) into L: every
 // stream's loads issued back to back before the first wait.  Padding slots
 // of the stream bucket are not loaded: their registers are free registers of
 // the pass, written before they are read.
@@ -317,6 +359,12 @@ __device__ __forceinline__ void vm_load(const VmParams& P, T (&L)[NINB][E], int6
             realign_load<T, V>(row_base<T>(Q.in[a], row0 + u, cbase - PG::realign[a]), loff, RW[a][u], RN[a][u]);
             continue;
           }
+          if (PG::bcol[a]) {   // a value per row
+            const T w = *(const T*)row_base<T>(Q.in[a], row0 + u, 0);
+#pragma unroll
+            for (int v = 0; v < V; ++v) L[a][u * V + v] = w;
+            continue;
+          }
           const vecA w = *(const vecA*)(row_base<T>(Q.in[a], row0 + u, cbase) + loff);
 #pragma unroll
           for (int v = 0; v < V; ++v) L[a][u * V + v] = w[v];
@@ -336,38 +384,54 @@ __device__ __forceinline__ void vm_load(const VmParams& P, T (&L)[NINB][E], int6
       return;
     }
   }
-  bool okv[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) okv[u] = ((vmask >> (u * V)) & ((1u << V) - 1)) != 0;
+  const bool split = mode == MODE_EDGE && split_lane<V, U>(vmask);
 #pragma unroll
   for (int a = 0; a < NINB; ++a) {
     if (a >= n_in_of<PG>(P)) break;
     const T* b = (const T*)Q.in[a].base;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
+      const unsigned m = row_mask<V>(vmask, u);
+      if (PG::COMPILED && PG::bcol[a]) {
+        const T w = b[(m != 0 ? row0 + u : 0) * Q.in[a].s_row];
+#pragma unroll
+        for (int v = 0; v < V; ++v) L[a][u * V + v] = w;
+        continue;
+      }
       const T* p = b + (row0 + u) * Q.in[a].s_row + c0;
-      if (mode == MODE_CLAMP) p = okv[u] ? p : b;
+      if (mode == MODE_EDGE) p = m != 0 ? p + edge_shift<V>(m) : b;
       const vecA w = *(const vecA*)p;
 #pragma unroll
       for (int v = 0; v < V; ++v) L[a][u * V + v] = w[v];
     }
   }
-  if (mode == MODE_CLAMP) {
+  if (split) {
 #pragma unroll
     for (int a = 0; a < NINB; ++a) {
-      if (PG::COMPILED && a >= n_in_of<PG>(P)) break;
+      if (a >= n_in_of<PG>(P)) break;
+      if (PG::COMPILED && PG::bcol[a]) continue;
 #pragma unroll
-      for (int e = 0; e < E; ++e) L[a][e] = ((vmask >> e) & 1) ? L[a][e] : (T)0;
+      for (int u = 0; u < U; ++u) {
+        const int sh = edge_shift<V>(row_mask<V>(vmask, u));
+        vecA w;
+#pragma unroll
+        for (int v = 0; v < V; ++v) w[v] = L[a][u * V + v];
+#pragma unroll
+        for (int v = 0; v < V; ++v) L[a][u * V + v] = edge_elem<T, V>(w, sh, v);
+      }
     }
   }
 }
 
 // One step: U rows of the tile, V columns per lane.
-//   MODE_FAST : every slot of every lane valid, unit column strides: vector
-//               loads of all streams issued back to back.
-//   MODE_CLAMP: validity is whole V-vectors (unit strides, widths multiple
-//               of V): the same vector loads with invalid lanes pointed at
-//               the stream's first element and zeroed.
+//   MODE_FAST : every slot of every lane valid, unit column strides (in a
+//               compiled pass also inputs of column stride 0: a value per
+//               row): vector loads of all streams issued back to back.
+//   MODE_EDGE : the same strides, some slots outside the space: the same
+//               vector loads, lanes outside pointed at the stream's first
+//               element, a lane across the boundary at the vector that ends
+//               there (edge_shift).  What is outside is never stored nor
+//               added.
 //   MODE_SLOW : per-element masked accesses, one stream at a time.
 // Slots n_in..NINB-1 of the bucket read a 4 KB zero page in the vector modes.
 // With SPLIT the caller has instead issued the step's loads into L (see
@@ -375,14 +439,11 @@ __device__ __forceinline__ void vm_load(const VmParams& P, T (&L)[NINB][E], int6
 // step (row next_row0, known to be MODE_FAST) are issued into L as soon as
 // this step's values are in registers, so they are in flight during the op
 // list and the stores.
-// SPMV_RT (with SPMV): the SpMV prologue runs only for passes that have one
-// (P.spmv), so one instantiation serves SpMV and elementwise passes alike
-// (the batched executor's).
 // STG: the step's staged streams (P.st_on) come from the wave's LDS slice
 // `stl` at chunk row q (vm_stencil_tile), the others from global memory;
 // MODE_FAST only.
-template <typename T, int HV, bool SPMV, int NR, int NINB, bool SPLIT, int ROWS, bool SPMV_RT = false,
-          bool STG = false, class PG = VmInterp>
+template <typename T, int HV, bool SPMV, int NR, int NINB, bool SPLIT, int ROWS, bool STG = false,
+          class PG = VmInterp>
 __device__ __forceinline__ void vm_step(
     const VmParams& P,
     typename GVec<T, Shape<T, HV, SPMV, NR, ROWS>::GS>::type (&R0)[NR],
@@ -451,6 +512,12 @@ __device__ __forceinline__ void vm_step(
           realign_load<T, V>(row_base<T>(Q.in[a], row0 + u, cbase - PG::realign[a]), loff, RW[a][u], RN[a][u]);
           continue;
         }
+        if (PG::bcol[a]) {   // a value per row
+          const T w = *(const T*)row_base<T>(Q.in[a], row0 + u, 0);
+#pragma unroll
+          for (int v = 0; v < V; ++v) RSET(a, u * V + v, w);
+          continue;
+        }
         const vecA w = *(const vecA*)(row_base<T>(Q.in[a], row0 + u, cbase) + loff);
 #pragma unroll
         for (int v = 0; v < V; ++v) RSET(a, u * V + v, w[v]);
@@ -471,9 +538,7 @@ __device__ __forceinline__ void vm_step(
     // every stream of the bucket, padding slots from a zero page, in flight
     // before the first wait (a compiled pass loads its own streams only)
     T Ls[NINB][E];
-    bool okv[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) okv[u] = ((vmask >> (u * V)) & ((1u << V) - 1)) != 0;
+    const bool split = mode == MODE_EDGE && split_lane<V, U>(vmask);
 #pragma unroll
     for (int a = 0; a < NINB; ++a) {
       if (PG::COMPILED && a >= n_in_of<PG>(P)) break;
@@ -482,19 +547,34 @@ __device__ __forceinline__ void vm_step(
       const int64_t cc = c0 & (-Q.in[a].s_col);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
+        const unsigned m = row_mask<V>(vmask, u);
+        if (PG::COMPILED && PG::bcol[a]) {
+          const T w = b[(m != 0 ? row0 + u : 0) * Q.in[a].s_row];
+#pragma unroll
+          for (int v = 0; v < V; ++v) Ls[a][u * V + v] = w;
+          continue;
+        }
         const T* p = b + (row0 + u) * Q.in[a].s_row + cc;
-        if (mode == MODE_CLAMP) p = okv[u] ? p : b;
+        if (mode == MODE_EDGE) p = m != 0 && Q.in[a].s_col != 0 ? p + edge_shift<V>(m) : b;
         const vecA w = *(const vecA*)p;
 #pragma unroll
         for (int v = 0; v < V; ++v) Ls[a][u * V + v] = w[v];
       }
     }
-    if (mode == MODE_CLAMP) {
+    if (split) {
 #pragma unroll
       for (int a = 0; a < NINB; ++a) {
-        if (PG::COMPILED && a >= n_in_of<PG>(P)) break;
+        if (a >= n_in_of<PG>(P)) break;
+        if (PG::COMPILED && PG::bcol[a]) continue;
 #pragma unroll
-        for (int e = 0; e < E; ++e) Ls[a][e] = ((vmask >> e) & 1) ? Ls[a][e] : (T)0;
+        for (int u = 0; u < U; ++u) {
+          const int sh = edge_shift<V>(row_mask<V>(vmask, u));
+          vecA w;
+#pragma unroll
+          for (int v = 0; v < V; ++v) w[v] = Ls[a][u * V + v];
+#pragma unroll
+          for (int v = 0; v < V; ++v) Ls[a][u * V + v] = edge_elem<T, V>(w, sh, v);
+        }
       }
     }
 #pragma unroll
@@ -541,9 +621,9 @@ __device__ __forceinline__ void vm_step(
   }
   if constexpr (SPMV) {
     static_assert(U == 1, "SpMV steps take one row of the tiling");
-    if (!SPMV_RT || P.spmv) {
+    {
       T y[4];
-      if (!SPMV_RT && P.sp_coop) {
+      if (P.sp_coop) {
         // rows computed by the whole block before the tile (vm_kernel)
         extern __shared__ __attribute__((aligned(16))) char vm_dyn_lds[];
         const T* yt = (const T*)vm_dyn_lds;
@@ -596,8 +676,13 @@ __device__ __forceinline__ void vm_step(
           if (PG::COMPILED && mode == MODE_FAST)
             *(vecA*)(row_base<T>(Q.out[s], row0 + u, cbase) + (uint32_t)((threadIdx.x & (WAVE - 1)) * V * sizeof(T))) =
                 w;
-          else if (mode == MODE_FAST) *(vecA*)(b + (row0 + u) * sr + c0) = w;
-          else if ((vmask >> (u * V)) & 1) *(vecA*)(b + (row0 + u) * sr + c0) = w;
+          else if (mode == MODE_FAST || row_mask<V>(vmask, u) == (1u << V) - 1)
+            *(vecA*)(b + (row0 + u) * sr + c0) = w;
+          else if (const unsigned m = row_mask<V>(vmask, u); m != 0) {
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+              if ((m >> v) & 1) b[(row0 + u) * sr + c0 + v] = w[v];
+          }
         }
       }
     }
@@ -868,7 +953,7 @@ __device__ __forceinline__ void vm_stencil_tile(
     }
     const T* cur = sl + (size_t)(c % ST_NBUF) * SR * PITCH;
     for (int q = 0; q < ST_RCH; q += U)
-      vm_step<T, HV, SPMV, NR, NINB, false, ROWS, false, true, PG>(P, R0, R1, R2, R3, G, L,
+      vm_step<T, HV, SPMV, NR, NINB, false, ROWS, true, PG>(P, R0, R1, R2, R3, G, L,
                                                                tr * RED_TH + (int64_t)c * ST_RCH + q, c0,
                                                                (1u << E) - 1, MODE_FAST, false, 0, nullptr, nullptr,
                                                                cur, q, cbase);
@@ -902,7 +987,7 @@ void vm_kernel(const VmParams P) {
 
   // a compiled one-block pass first reduces an earlier pass's block sums
   // (P.fin), in place of the block-sum kernel's launch
-  if constexpr (PG::COMPILED) {
+  if constexpr (PG::COMPILED && PG::FIN) {
     if (P.fin.n_red > 0) {
       fin_sums<T, BLOCK / WAVE, FIN_MAX_CHUNKS>(P.fin);
       __syncthreads();
@@ -976,7 +1061,7 @@ void vm_kernel(const VmParams P) {
   // (red_split, compiled passes with one reduction: block lb owns tile lb
   // and its four waves take a quarter of the rows each)
   const int split = P.row_split > 1 ? P.row_split : 1;
-  const bool rsplit = PG::COMPILED && P.red_split != 0;
+  const bool rsplit = PG::COMPILED && PG::RSPLIT && P.red_split != 0;
   const int rsb = rsplit ? P.red_split : 1;   // blocks per tile
   const int64_t t_begin = rsplit ? (int64_t)(lb / rsb) : split > 1 ? gw / split : gw * P.tiles_per_wave;
   const int64_t t_end = min(t_begin + ((split > 1 || rsplit) ? 1 : P.tiles_per_wave), P.n_tiles);
@@ -1012,6 +1097,9 @@ void vm_kernel(const VmParams P) {
     const int64_t c0 = cbase + (int64_t)lane * V;
     G.acc0 = G.acc1 = G.acc2 = G.acc3 = (T)0;
     if constexpr (PG::COMPILED) {
+      G.dsum = nullptr;
+    }
+    if constexpr (PG::COMPILED && PG::RSPLIT) {
       extern __shared__ __attribute__((aligned(16))) char vm_dyn_lds[];
       G.dsum = !rsplit ? nullptr : rsb > 1 ? (T*)P.red_partials[0] : (T*)vm_dyn_lds;
     }
@@ -1038,8 +1126,8 @@ void vm_kernel(const VmParams P) {
                                            cbase + TW + (PG::REALIGN ? V : 0) <= DFX_C(cols));
       int mode = MODE_FAST;
       unsigned vmask = (1u << E) - 1;
-      if (!(DFX_C(unit_cols) && interior)) {
-        mode = DFX_C(vec_cols) ? MODE_CLAMP : MODE_SLOW;
+      if (!(DFX_C(lin_cols) && interior)) {
+        mode = DFX_C(lin_cols) ? MODE_EDGE : MODE_SLOW;
         vmask = 0;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
@@ -1055,20 +1143,20 @@ void vm_kernel(const VmParams P) {
           vm_load<T, V, U, E, NINB, PG>(P, L, row0, c0, vmask, mode, cbase);
       if constexpr (PF) {
         const int64_t nr = row0 + U;
-        next_fast = r + U < r_hi && DFX_C(unit_cols) &&
+        next_fast = r + U < r_hi && DFX_C(lin_cols) &&
                     (DFX_C(is1d) ? ((nr + U) * TW <= DFX_C(n1d))
                                  : (nr + U <= DFX_C(rows) && cbase >= (PG::REALIGN ? V : 0) &&
                                     cbase + TW + (PG::REALIGN ? V : 0) <= DFX_C(cols)));
       }
       if constexpr (PG::COMPILED) G.drow = r;
-      vm_step<T, HV, SPMV, NR, NINB, SPLIT, ROWS, false, false, PG>(P, R0, R1, R2, R3, G, L, row0, c0, vmask, mode,
+      vm_step<T, HV, SPMV, NR, NINB, SPLIT, ROWS, false, PG>(P, R0, R1, R2, R3, G, L, row0, c0, vmask, mode,
                                                                     next_fast, row0 + U, sp_col[SPMV ? wib : 0],
                                                                     sp_val[SPMV ? wib : 0], nullptr, 0, cbase);
 #undef DFX_C
       have = next_fast;
     }
     // ---- tile sums into the block's LDS row ---------------------------------------
-    if (P.n_red > 0 && !rsplit) {
+    if ((PG::COMPILED ? PG::N_RED : P.n_red) > 0 && !rsplit) {
       const int j = wib * (int)P.tiles_per_wave + (int)(t - t_begin);
       T a0 = wave_sum(G.acc0);
       if (lane == 0) tsum[0][j] = a0;
@@ -1078,8 +1166,8 @@ void vm_kernel(const VmParams P) {
     }
   }
 
-  if (P.n_red == 0) return;
-  if constexpr (PG::COMPILED) {
+  if ((PG::COMPILED ? PG::N_RED : P.n_red) == 0) return;
+  if constexpr (PG::COMPILED && PG::RSPLIT) {
     if (rsplit) {
       // several blocks: the summands are in the workspace, for the
       // block-sum reduction (VmFinal.tile)
