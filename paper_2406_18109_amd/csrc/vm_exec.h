@@ -676,12 +676,15 @@ __device__ __forceinline__ void vm_step(
           if (PG::COMPILED && mode == MODE_FAST)
             *(vecA*)(row_base<T>(Q.out[s], row0 + u, cbase) + (uint32_t)((threadIdx.x & (WAVE - 1)) * V * sizeof(T))) =
                 w;
-          else if (mode == MODE_FAST || row_mask<V>(vmask, u) == (1u << V) - 1)
-            *(vecA*)(b + (row0 + u) * sr + c0) = w;
-          else if (const unsigned m = row_mask<V>(vmask, u); m != 0) {
+          else if (mode == MODE_FAST) *(vecA*)(b + (row0 + u) * sr + c0) = w;
+          else {
+            const unsigned m = row_mask<V>(vmask, u);
+            if (m == (1u << V) - 1) *(vecA*)(b + (row0 + u) * sr + c0) = w;
+            else if (m != 0) {
 #pragma unroll
-            for (int v = 0; v < V; ++v)
-              if ((m >> v) & 1) b[(row0 + u) * sr + c0 + v] = w[v];
+              for (int v = 0; v < V; ++v)
+                if ((m >> v) & 1) b[(row0 + u) * sr + c0 + v] = w[v];
+            }
           }
         }
       }
