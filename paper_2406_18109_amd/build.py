@@ -40,13 +40,14 @@ SOURCES = [
     ("vm_tier3.hip", True),
     ("serve.hip", True),
     ("batch.hip", True),
+    ("coop.hip", True),
 ]
 
 
 # Headers a compiled pass is built from at run time (hiprtc): the op-list
 # kernel template and what it includes, embedded in the library so that a
 # compiled pass always matches the interpreter it replaces.
-JIT_HEADERS = ["vm_exec.h", "vm_instr.inc", "vm.h", "dev_common.h", "dmath.h", "dmath_coef.h"]
+JIT_HEADERS = ["vm_exec.h", "coop_exec.h", "vm_instr.inc", "vm.h", "dev_common.h", "dmath.h", "dmath_coef.h"]
 
 
 def _c_string(text: str) -> str:

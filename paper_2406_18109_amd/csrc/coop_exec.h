@@ -150,12 +150,12 @@ __device__ __forceinline__ void coop_spmv(const PT& P, const int64_t base, T* yt
 // of the block; lds: coop_lds_bytes, tot: VM_MAXRED values in LDS that
 // receive the tile's sums (from lane 0 of wave k; the caller's next barrier
 // publishes them).  The pass's global stores are issued, not waited for.
-template <typename T, int HV, class PT>
+template <typename T, int HV, int NW = COOP_WAVES, class PG = VmInterp, class PT>
 __device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* lds, T* tot) {
-  // rows per step: both of the wave's in arithmetic kernels; one in the
-  // transcendental ones (their handlers need the registers: 1024 threads
-  // leave 128 per lane)
-  typedef Shape<T, HV, false, VM_NREG_LIGHT, (HV > 0 ? 1 : COOP_RPW)> S;
+  constexpr int RPW = RED_TH / NW;   // rows per wave
+  // rows per step: two in arithmetic kernels; one in the transcendental ones
+  // (their handlers need the registers: 1024 threads leave 128 per lane)
+  typedef Shape<T, HV, false, VM_NREG_LIGHT, (HV > 0 ? 1 : 2)> S;
   constexpr bool HEAVY = S::HEAVY;
   constexpr int V = S::V, U = S::U, TW = S::TW, E = S::E, GS = S::GS, NG = S::NG, NR = VM_NREG_LIGHT, NINB = 6;
   typedef typename GVec<T, GS>::type gvec;
@@ -166,17 +166,26 @@ __device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* ld
   // (a space has at most 2^20 tiles)
   const int64_t tr = P.strips == 1 ? t : (int64_t)((uint32_t)t / (uint32_t)P.strips);
   const int64_t cbase = (t - tr * P.strips) * TW;
-  const int64_t row_w = tr * RED_TH + wib * COOP_RPW;   // this wave's first row
+  const int64_t row_w = tr * RED_TH + wib * RPW;   // this wave's first row
   const bool is1d = P.is1d != 0;
   if (row_w < P.rows) {
     gvec R0[NR], R1[NR], R2[NR], R3[NR];
     VmState<T, NG, GS> G;
-    T* yt = dsum + wib * COOP_RPW * TW;   // this wave's rows of slot 0
-    if (P.spmv) coop_spmv<T, COOP_RPW * TW / WAVE>(P, row_w * TW, yt);
-    for (int k = 0; k < P.n_bc; ++k) {
-      const gvec v = (gvec)load_0d<T>(P.bc[k]);
-      const int r = P.bc_reg[k];
-      FOR_G(Rg[r] = v;)
+    T* yt = dsum + wib * RPW * TW;   // this wave's rows of slot 0
+    if (P.spmv) coop_spmv<T, RPW * TW / WAVE>(P, row_w * TW, yt);
+    if constexpr (PG::COMPILED) {
+#pragma unroll
+      for (int k = 0; k < VM_MAXBC; ++k) {
+        if (k >= P.n_bc) break;
+        const gvec v = (gvec)load_0d<T>(P.bc[k]);
+        FOR_G(Rg[PG::bc_reg[k]] = v;)
+      }
+    } else {
+      for (int k = 0; k < P.n_bc; ++k) {
+        const gvec v = (gvec)load_0d<T>(P.bc[k]);
+        const int r = P.bc_reg[k];
+        FOR_G(Rg[r] = v;)
+      }
     }
 #pragma unroll
     for (int g = 0; g < NG; ++g) G.z[g] = (gvec)(T)0;
@@ -184,8 +193,8 @@ __device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* ld
     // 1-D passes of unit stride: every stream at one 32-bit offset from its
     // scalar base (the wave's first element)
     const bool line = is1d && P.unit_cols;
-    const int left = is1d ? (int)min(P.n1d - row_w * TW, (int64_t)COOP_RPW * TW) : 0;
-    for (int u0 = 0; u0 < COOP_RPW; u0 += U) {
+    const int left = is1d ? (int)min(P.n1d - row_w * TW, (int64_t)RPW * TW) : 0;
+    for (int u0 = 0; u0 < RPW; u0 += U) {
       const int64_t row0 = row_w + u0;
       if (row0 >= P.rows) break;
       const int i0 = u0 * TW + lane * V;   // the lane's first element from the wave's
@@ -216,7 +225,7 @@ __device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* ld
     else if (g_ == 2) gset<T, GS>(R2[a], (e) % GS, x); else gset<T, GS>(R3[a], (e) % GS, x); }
 #pragma unroll
       for (int a = 0; a < NINB; ++a) {
-        if (a >= P.n_in) break;
+        if (a >= (PG::COMPILED ? PG::N_IN : P.n_in)) break;
         const int64_t sr = P.in[a].s_row, sc = P.in[a].s_col;
         const T* b = global_ptr<const T>(P.in[a].base) + row0 * sr;
         if (fast) {
@@ -246,8 +255,10 @@ __device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* ld
         for (int e = 0; e < E; ++e) COOP_RSET(NR - 1, e, yt[(u0 + e / V) * TW + lane * V + e % V]);
       }
 #undef COOP_RSET
-      G.drow = wib * COOP_RPW + u0;
-      {
+      G.drow = wib * RPW + u0;
+      if constexpr (PG::COMPILED) {
+        PG::template run<T, HV, NR, NG, GS, E>(R0, R1, R2, R3, G, vmask);
+      } else {
         constexpr bool DEFER_OK = true;
         VmInstr nx = P.code[0];
         for (int pc = 0; pc < P.n_code; ++pc) {
@@ -263,8 +274,11 @@ __device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* ld
 #include "vm_instr.inc"
         }
       }
-      for (int s = 0; s < P.n_out; ++s) {
-        const int o = P.out_reg[s];
+      // (one loop for both: a shared lambda spilled the batched executor's
+      // registers, 34 -> 40 ms for 32 solves)
+#pragma unroll(PG::COMPILED ? VM_MAXOUT : 1)
+      for (int s = 0; s < (PG::COMPILED ? PG::N_OUT : P.n_out); ++s) {
+        const int o = PG::COMPILED ? PG::out_reg[s] : P.out_reg[s];
         gvec ev[NG];
         FOR_G(ev[g] = Rg[o];)
         const int64_t sr = P.out[s].s_row, sc = P.out[s].s_col;
@@ -295,6 +309,32 @@ __device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* ld
                                       P.cols, cbase);
     const T v = wave_sum(acc);
     if (lane == 0) tot[wib] = v;
+  }
+}
+
+// One ordinary pass with a block of NW waves for every tile (the rule and its
+// measurements: coop_pass in core.cpp), interpreted or compiled.  Bound: with
+// a wave per tile the chain of 32 rows' loads (and, in SpMV, the row walks)
+// of one wave; here a wave has two rows, the lane sums run in their order
+// from LDS, and 16 waves per tile keep the gathers of x in flight (BiCGSTAB
+// over 150 cubed, 8 iterations: 4039 -> 2370 us).  The tile's sum has the
+// ordinary pass's bits; a lone block finishes its results itself
+// (red_direct), otherwise the block-sum reduction gets one sum per tile.
+template <typename T, int NW, class PG = VmInterp>
+__global__ __launch_bounds__(NW * WAVE) void coop_kernel(const VmParams P) {
+  extern __shared__ __attribute__((aligned(16))) char coop_dyn_lds[];
+  __shared__ T tot[VM_MAXRED];
+  coop_tile<T, 0, NW, PG>(P, (int64_t)blockIdx.x, coop_dyn_lds, tot);
+  // (wave k holds reduction k's tile sum)
+  const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  if (wib < P.n_red && (threadIdx.x & (WAVE - 1)) == 0) {
+    const T v = tot[wib];
+    if (P.red_direct) {
+      T* res = (T*)P.red_result[wib];
+      *res = P.red_init[wib] ? v : *res + v;
+    } else {
+      ((T*)P.red_partials[wib])[blockIdx.x] = v;
+    }
   }
 }
 

@@ -1246,7 +1246,7 @@ constexpr int64_t RED_SPLIT_MAX_TILES = 2048;
 // 32 waves of one row; DFX_RED_GLOB=<n> sets the blocks (1, 2, 4 or 8; 0: off)
 constexpr int RED_SPLIT_BLOCKS = 4;
 static size_t block_sum_slots(const PassPlan& p) {
-  int64_t n = std::max<int64_t>(p.grid, p.n_tiles <= RED_SPLIT_MAX_TILES ? p.n_tiles : 0);
+  int64_t n = std::max<int64_t>(p.grid, p.n_tiles <= NOALLOC_BLOCKS ? p.n_tiles : 0);
   if (p.n_tiles == 1 && p.red_cstore.size() == 1)
     n = std::max<int64_t>(n, (int64_t)RED_TH * (p.dtype == DFX_F64 ? Lanes<double>::TW : Lanes<float>::TW));
   return (size_t)n;
@@ -1473,6 +1473,38 @@ static int lin_cols(const PassPlan& p) {
   return 1;
 }
 
+static int staged_streams(const PassPlan& p, size_t n_stores);
+
+// Whether a pass runs with a block of 16 waves for every tile (coop_kernel).
+// A reducing pass cannot split its rows over blocks (a tile's sum is one
+// ordered chain), so with a wave per tile it has as many waves as tiles and
+// is bound by that wave's walk over 32 rows.  Measured (graph replay of 8
+// iterations, one wave per tile against a block per tile; 64 to 300 are
+// sides of 2-D systems, three-digit sides with 3-D are cubes):
+//   interpreted: CG 64 (1 tile) 807 -> 328 us, 100 (3 tiles) 1184 -> 373,
+//     300 (22) 1366 -> 397; CG 100 cubed (245) 1699 -> 598; the SpMV pass
+//     alone at 160 cubed (1000) 2167 -> 1644, at 200 cubed (1954) 2854 ->
+//     2867; the passes without SpMV at 128 cubed (512) 1054 -> 1048, at 160
+//     cubed 1644 -> 1891 (the ordinary kernel has enough waves by then and
+//     keeps its program in registers).
+//   compiled: CG 100 (3) 860 -> 256, 300 (22) 427 -> 279; BiCGSTAB 150 cubed
+//     (824) 4039 -> 2370; CG 256 cubed (4096) 5334 -> 4930, 290 cubed (5955)
+//     7814 -> 7110, 380 cubed (13397) 16950 -> 15627.  A lone tile of one
+//     reduction stays with red_split, which spreads it over several blocks
+//     (CG 64: 209 against 232 us).
+// Two reductions are what 64 KB of LDS hold.  Above NOALLOC_BLOCKS tiles the
+// block sums would no longer fit the fixed scratch.  DFX_COOP=0 turns it off.
+constexpr int64_t COOP_VM_TILES = 512, COOP_VM_SPMV_TILES = 1024;
+static bool coop_pass(const PassPlan& p, bool compiled) {
+  const char* e = std::getenv("DFX_COOP");
+  if (e && e[0] == '0') return false;
+  if (p.kind == 2 || p.tier != TIER_ARITH || p.red_cstore.empty() || p.red_cstore.size() > 2 || p.ins.size() > 6 ||
+      !p.unit_cols || p.n_tiles < 1 || staged_streams(p, SIZE_MAX) > 0)
+    return false;
+  if (!compiled) return p.n_tiles <= (p.kind == 1 ? COOP_VM_SPMV_TILES : COOP_VM_TILES);
+  return (p.n_tiles > 1 || p.red_cstore.size() > 1) && p.n_tiles <= NOALLOC_BLOCKS;
+}
+
 // Passes that run compiled when jit is on (measured on MI355X):
 // transcendental passes, where the interpreter's dispatch dominates
 // (Black-Scholes FP64 over 2^26 options: 0.79 against 1.05 ms); small
@@ -1491,7 +1523,8 @@ static bool jit_wanted(const PassPlan& p, int st_n) {
   if (all && all[0] == '1') return true;
   int64_t small = 1024;
   if (const char* e = std::getenv("DFX_JIT_SMALL")) small = std::atoll(e);
-  return p.tier != TIER_ARITH || p.n_tiles < small || st_n > 0 || (lin_cols(p) && !p.unit_cols);
+  return p.tier != TIER_ARITH || p.n_tiles < small || st_n > 0 || (lin_cols(p) && !p.unit_cols) ||
+         coop_pass(p, true);
 }
 
 // The pass's program and kernel variant for compilation (rows: the rows per
@@ -1518,7 +1551,9 @@ static std::shared_ptr<JitEntry> request_compiled(PassPlan& p, int st_n, int row
       g.st_dr.push_back(p.st_dr[a]);
       g.st_dc.push_back(p.st_dc[a]);
     }
-  const JitVariant v = jit_variant(p.dtype == DFX_F64, p.tier, (int)p.ins.size(), p.kind == 1, st_n, rows);
+  JitVariant v = jit_variant(p.dtype == DFX_F64, p.tier, (int)p.ins.size(), p.kind == 1, st_n, rows);
+  p.jit_coop = coop_pass(p, true);
+  if (p.jit_coop) v.coop = COOP_WAVES;
   std::string name;
   const std::string src = jit_source(v, g, &name);
   return jit_request(src, name, sync);
@@ -1727,12 +1762,14 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
       p.realign_shift = ra_shift;
       if (jit_wanted(p, P.st_n) || ra_shift > 0) p.jit = request_compiled(p, P.st_n, rows, c.cfg.jit == 2);
     }
-    if (p.jit && ra == p.realign) fn = jit_function(*p.jit, c.cfg.device, !c.capturing);
+    if (p.jit && ra == p.realign && p.jit_coop == coop_pass(p, true))
+      fn = jit_function(*p.jit, c.cfg.device, !c.capturing);
     if (fn) P.lin_cols = lin_cols(p) && edge_ok(p);
   }
+  const bool coop = coop_pass(p, fn != nullptr);
   // column shift (aligned output vectors), then row split, of passes
   // without reductions; either changes the launch shape only
-  const int cs_shift = fn && ra_shift > 0 ? ra_shift : col_shift_for(p, P, es);
+  const int cs_shift = coop ? 0 : fn && ra_shift > 0 ? ra_shift : col_shift_for(p, P, es);
   if (const int cs = cs_shift; cs > 0) {
     const int64_t TWp = p.dtype == DFX_F64 ? Lanes<double>::TW : Lanes<float>::TW;
     const int64_t row_tiles = p.n_tiles / std::max<int64_t>(1, p.strips);
@@ -1741,14 +1778,14 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
     P.n_tiles = row_tiles * P.strips;
     P.grid = grid_for((P.n_tiles + p.tiles_per_wave - 1) / p.tiles_per_wave);
   }
-  if (const int rs = row_split_for(p, P); rs > 1) {
+  if (const int rs = coop ? 1 : row_split_for(p, P); rs > 1) {
     P.row_split = rs;
     P.sp_coop = 0;
     P.grid = grid_for(P.n_tiles * rs);
   }
-  // a compiled pass of one reduction and few tiles gives each tile a block
-  // of four waves (red_split; bit-identical tile sums)
-  if (fn && red_split_ok(p, P)) {
+  // other compiled passes of one reduction and few tiles give each tile a
+  // block of four waves (red_split; bit-identical tile sums)
+  if (fn && !coop && red_split_ok(p, P)) {
     // a one-tile pass spreads its rows over RED_SPLIT_BLOCKS blocks (two
     // rows per wave) and leaves the ordered sum of the summands to the
     // block-sum reduction, which the next compiled one-block pass (the
@@ -1778,6 +1815,17 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
       }
     }
   }
+  if (coop) {
+    P.grid = (int)p.n_tiles;
+    P.sp_coop = 0;
+    F.nblocks = (int)p.n_tiles;
+    if (P.red_direct && p.n_tiles > 1) {
+      // the block-sum reduction now follows (count_launches assumed none)
+      P.red_direct = 0;
+      c.stats.launches += 1;
+      if (c.capturing) c.capture_launches += 1;
+    }
+  }
   // Block sums an earlier pass left waiting: a compiled one-block pass of
   // the same element type reduces them first, in its own launch (the same
   // tree as the block-sum kernel); a pass that reduces (its block sums may
@@ -1789,7 +1837,7 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
   if (c.fin_pending) {
     const char* fa = std::getenv("DFX_FIN_ATTACH");
     const bool fin_attach = !(fa && fa[0] == '0');
-    if (fin_attach && fn && P.grid == 1 && p.n_tiles <= 4 * p.tiles_per_wave && c.fin_f64 == (p.dtype == DFX_F64 ? 1 : 0) &&
+    if (fin_attach && fn && !coop && P.grid == 1 && p.n_tiles <= 4 * p.tiles_per_wave && c.fin_f64 == (p.dtype == DFX_F64 ? 1 : 0) &&
         c.fin.nblocks <= FIN_MAX_CHUNKS * FINAL_CHUNK) {
       P.fin = c.fin;
       c.fin_pending = false;
@@ -1801,13 +1849,16 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
   }
   if (timed) (void)hipEventRecord(p.ev0, c.stream);
   if (e != 0) {
+  } else if (coop && !fn) {
+    e = launch_coop(P, p.dtype == DFX_F64, c.stream);
   } else if (fn) {
     const JitVariant v = jit_variant(p.dtype == DFX_F64, p.tier, P.n_in, P.spmv, P.st_n, rows);
-    size_t lds = vm_dyn_lds_bytes(P, v.sten != 0);
+    size_t lds = coop ? coop_lds(P.n_red, P.spmv != 0) : vm_dyn_lds_bytes(P, v.sten != 0);
     if (ra_shift > 0) lds = std::max(lds, REALIGN_LDS);
     if (v.sten) lds = std::max(lds, STENCIL_LDS);
     void* args[] = {(void*)&P};
-    e = (int)hipModuleLaunchKernel(fn, (unsigned)P.grid, 1, 1, BLOCK, 1, 1, (unsigned)lds, c.stream, args, nullptr);
+    e = (int)hipModuleLaunchKernel(fn, (unsigned)P.grid, 1, 1, coop ? COOP_BLOCK : BLOCK, 1, 1, (unsigned)lds, c.stream,
+                                   args, nullptr);
     c.stats.compiled_launches += 1;
     if (c.capturing) c.capture_compiled += 1;
   } else {

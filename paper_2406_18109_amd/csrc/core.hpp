@@ -17,6 +17,7 @@ namespace dfx {
 
 int launch_vm(const VmParams& P, int is_f64, int tier, int rows, hipStream_t stream);
 int arith_waves_per_cu(int is_f64, int n_in, int rows);
+int launch_coop(const VmParams& P, int is_f64, hipStream_t stream);
 int launch_vm_final(const VmFinal& F, int is_f64, hipStream_t stream);
 int stream_bucket(int n_in, int tier);
 int scratch_address(int device, void** out);
@@ -134,6 +135,7 @@ struct PassPlan {
   // execution, shared by every plan with the same program and variant
   std::shared_ptr<JitEntry> jit;
   bool jit_checked = false;   // whether the pass runs compiled is decided
+  bool jit_coop = false;      // it was compiled as a coop_kernel
 };
 
 struct Plan {

@@ -319,7 +319,7 @@ std::string jit_source(const JitVariant& v, const JitProgram& g, std::string* na
   const bool f64 = v.is_f64 != 0;
   std::string s;
   s += "// One fused pass of the dfx executor, compiled for its op list.\n";
-  s += "#include \"vm_exec.h\"\n\nnamespace dfx {\n\nstruct JitPass {\n";
+  s += std::string("#include \"") + (v.coop ? "coop_exec.h" : "vm_exec.h") + "\"\n\nnamespace dfx {\n\nstruct JitPass {\n";
   s += "  static constexpr bool COMPILED = true;\n";
   s += "  static constexpr int WAVES = " + std::to_string(v.waves) + ";\n";
   s += std::string("  static constexpr bool HEAVY_PF = ") + (v.heavy_pf ? "true" : "false") + ";\n";
@@ -352,7 +352,8 @@ std::string jit_source(const JitVariant& v, const JitProgram& g, std::string* na
   for (const VmInstr& I : g.code) put_instr(s, I, f64);
   s += "#undef DFX_I\n  }\n};\n\n}  // namespace dfx\n";
   char ne[256];
-  std::snprintf(ne, sizeof(ne), "dfx::vm_kernel<%s, %d, %s, %d, %d, %d, %s, dfx::JitPass>", f64 ? "double" : "float",
+  if (v.coop) std::snprintf(ne, sizeof(ne), "dfx::coop_kernel<%s, %d, dfx::JitPass>", f64 ? "double" : "float", v.coop);
+  else std::snprintf(ne, sizeof(ne), "dfx::vm_kernel<%s, %d, %s, %d, %d, %d, %s, dfx::JitPass>", f64 ? "double" : "float",
                 v.hv, v.spmv ? "true" : "false", v.nr, v.nb, v.rows, v.sten ? "true" : "false");
   if (name_expr) *name_expr = ne;
   return s;

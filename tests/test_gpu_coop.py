@@ -106,3 +106,45 @@ def test_batch_spmv_rows_of_every_length(nnz_row):
         c.close()
     for g, r in zip(*out):
         assert np.array_equal(g, r)
+
+
+def _pass_results(n, dtype, monkeypatch, coop, **cfg):
+    monkeypatch.setenv("DFX_COOP", "1" if coop else "0")
+    c = dfx.Context(device=0, window_size=8, **cfg)
+    h = _stores(c, n, dtype, _mats(n))
+    for _ in range(2):
+        _tasks(c, h, n)
+    out = _read(c, h, n, dtype)
+    c.close()
+    return out
+
+
+@pytest.mark.parametrize("jit", [0, 2])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n", [1, 127, 129, 4095, 4096, 4097, 8193, 16385, 70001])
+def test_pass_with_a_block_per_tile_equals_ordinary(n, dtype, jit, monkeypatch):
+    """Reducing passes over one tile, 2 to 4 (one block of the ordinary kernel)
+    and more, ending in a partial row or tile, with one and two reductions."""
+    want = _pass_results(n, dtype, monkeypatch, False, fuse=False)
+    got = _pass_results(n, dtype, monkeypatch, True, jit=jit)
+    for a, b in zip(got, want):
+        np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("jit", [0, 2])
+@pytest.mark.parametrize("shape", [(1, 1), (33, 127), (31, 129), (70, 300), (4100, 3)])
+def test_2d_sum_with_a_block_per_tile(shape, jit, monkeypatch):
+    """Two-dimensional reductions with ragged rows and strips."""
+    res = []
+    for coop in (False, True):
+        monkeypatch.setenv("DFX_COOP", "1" if coop else "0")
+        c = dfx.Context(device=0, window_size=4, fuse=coop, jit=jit if coop else 0)
+        v = synth.uniform(90, 0, shape[0] * shape[1], -1.0, 1.0).reshape(shape)
+        x, y, s = upload(c, v), upload(c, np.zeros(shape)), upload(c, np.zeros(()))
+        T, N = c.part_tiling(list(shape)), c.part_none()
+        c.submit("mul_imm", [1, 1], [(x, T, "R"), (y, T, "W")], (3.0,))
+        c.submit("sum", [1, 1], [(y, T, "R"), (s, N, "Rd")], (1,))
+        res.append((c.store_read(y, list(shape), "f64"), c.store_read(s, [], "f64")))
+        c.close()
+    for a, b in zip(res[1], res[0]):
+        np.testing.assert_array_equal(a, b)
