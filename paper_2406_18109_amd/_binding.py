@@ -101,6 +101,7 @@ class dfx_serve_counters(C.Structure):
 SOLVE_QUEUED, SOLVE_RUNNING, SOLVE_CONVERGED, SOLVE_MAXITER, SOLVE_BREAKDOWN = 0, 1, 2, 3, 4
 
 _lib = None
+_fast = None
 
 # name -> (restype, argtypes) for every exported call
 SIGNATURES = {
@@ -173,6 +174,14 @@ def lib():
         f = getattr(L, name)
         f.restype = res
         f.argtypes = args
+    # the calls made per task are marshalled in C (csrc/marshal.cpp, built
+    # with the library); bound once, before any context exists
+    from . import _marshal
+    _marshal.bind(tuple(C.cast(getattr(L, "dfx_" + n), C.c_void_p).value for n in
+                        ("submit", "store_create", "store_release", "proj_identity", "part_none", "part_tiling")),
+                  OPS, PRIV, DTYPES)
+    global _fast
+    _fast = _marshal
     _lib = L
     return L
 
@@ -268,6 +277,7 @@ class Context:
         if rc != 0:
             raise DfxError(rc, "dfx_create failed")
         self.h = h
+        self._addr = h.value
         self.device = device
 
     # -- helpers ------------------------------------------------------------
@@ -280,6 +290,7 @@ class Context:
         if getattr(self, "h", None):
             rc = self.L.dfx_destroy(self.h)
             self.h = None
+            self._addr = 0
             if rc != 0:
                 raise DfxError(rc, "dfx_destroy failed")
 
@@ -298,7 +309,12 @@ class Context:
             pass
 
     # -- stores --------------------------------------------------------------
+    # (the _fast calls take plain ints, floats, names, lists and tuples and
+    # return None, with no call made, for other argument types)
     def store_create(self, shape, dtype="f64") -> int:
+        h = _fast.store_create(self._addr, shape, dtype)
+        if h is not None:
+            return h if h >= 0 else self._chk(h)
         out = C.c_int64()
         self._chk(self.L.dfx_store_create(self.h, len(shape), _i64(shape), _dt(dtype), C.byref(out)))
         return out.value
@@ -323,7 +339,11 @@ class Context:
         return p.value or 0
 
     def store_release(self, s: int):
-        self._chk(self.L.dfx_store_release(self.h, s))
+        rc = _fast.store_release(self._addr, s)
+        if rc is None:
+            rc = self.L.dfx_store_release(self.h, s)
+        if rc:
+            self._chk(rc)
 
     # -- projections / partitions ---------------------------------------------
     def proj_identity(self, ndim: int) -> int:
@@ -337,11 +357,18 @@ class Context:
         return out.value
 
     def part_none(self) -> int:
+        p = _fast.part_none(self._addr)
+        if p is not None:
+            return p if p >= 0 else self._chk(p)
         out = C.c_int32()
         self._chk(self.L.dfx_part_none(self.h, C.byref(out)))
         return out.value
 
     def part_tiling(self, tile, offset=None, proj=None) -> int:
+        if offset is None and proj is None:
+            p = _fast.part_tiling(self._addr, tile)
+            if p is not None:
+                return p if p >= 0 else self._chk(p)
         if offset is None:
             offset = [0] * len(tile)
         if proj is None:
@@ -358,6 +385,11 @@ class Context:
     # -- tasks ---------------------------------------------------------------
     def submit(self, op, launch, args, imm=()):
         """args: [(store, part, priv)] with priv in R/W/RW/Rd (int or name)."""
+        rc = _fast.submit(self._addr, op, launch, args, imm)
+        if rc is not None:
+            if rc:
+                self._chk(rc)
+            return
         opc = OPS[op] if isinstance(op, str) else int(op)
         A = (dfx_arg * max(1, len(args)))()
         for i, (s, p, pr) in enumerate(args):

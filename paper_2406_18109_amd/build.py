@@ -1,4 +1,5 @@
-"""Build libdfx.so (host core + gfx950 kernels) in-tree with hipcc.
+"""Build libdfx.so (host core + gfx950 kernels) in-tree with hipcc, and the
+binding's marshalling module with g++.
 
 `python -m paper_2406_18109_amd.build` or `build()`; compiles every source
 each call (objects in parallel) and links paper_2406_18109_amd/libdfx.so.
@@ -8,6 +9,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -93,8 +95,23 @@ def _compile(src: str, device: bool) -> str:
     return obj
 
 
+def build_marshal() -> str:
+    """The binding's argument marshalling (csrc/marshal.cpp), a CPython extension."""
+    out = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
+    tmp = out + ".tmp%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I" + sysconfig.get_paths()["include"],
+           "-I" + os.path.join(ROOT, "include"), os.path.join(CSRC, "marshal.cpp"), "-o", tmp]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        sys.stderr.write(r.stdout + r.stderr)
+        raise RuntimeError("compile failed: marshal.cpp")
+    os.replace(tmp, out)
+    return out
+
+
 def build(verbose: bool = False) -> str:
     write_jit_headers()
+    build_marshal()
     with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
         objs = list(ex.map(lambda s: _compile(*s), SOURCES))
     tmp = OUT + ".tmp%d" % os.getpid()
