@@ -385,6 +385,9 @@ __device__ __forceinline__ void vm_load(const VmParams& P, T (&L)[NINB][E], int6
     }
   }
   const bool split = mode == MODE_EDGE && split_lane<V, U>(vmask);
+  int sh[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) sh[u] = split ? edge_shift<V>(row_mask<V>(vmask, u)) : 0;
 #pragma unroll
   for (int a = 0; a < NINB; ++a) {
     if (a >= n_in_of<PG>(P)) break;
@@ -399,7 +402,7 @@ __device__ __forceinline__ void vm_load(const VmParams& P, T (&L)[NINB][E], int6
         continue;
       }
       const T* p = b + (row0 + u) * Q.in[a].s_row + c0;
-      if (mode == MODE_EDGE) p = m != 0 ? p + edge_shift<V>(m) : b;
+      if (mode == MODE_EDGE) p = m != 0 ? p + sh[u] : b;
       const vecA w = *(const vecA*)p;
 #pragma unroll
       for (int v = 0; v < V; ++v) L[a][u * V + v] = w[v];
@@ -412,12 +415,11 @@ __device__ __forceinline__ void vm_load(const VmParams& P, T (&L)[NINB][E], int6
       if (PG::COMPILED && PG::bcol[a]) continue;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int sh = edge_shift<V>(row_mask<V>(vmask, u));
         vecA w;
 #pragma unroll
         for (int v = 0; v < V; ++v) w[v] = L[a][u * V + v];
 #pragma unroll
-        for (int v = 0; v < V; ++v) L[a][u * V + v] = edge_elem<T, V>(w, sh, v);
+        for (int v = 0; v < V; ++v) L[a][u * V + v] = edge_elem<T, V>(w, sh[u], v);
       }
     }
   }
@@ -441,7 +443,7 @@ __device__ __forceinline__ void vm_load(const VmParams& P, T (&L)[NINB][E], int6
 // list and the stores.
 // STG: the step's staged streams (P.st_on) come from the wave's LDS slice
 // `stl` at chunk row q (vm_stencil_tile), the others from global memory;
-// MODE_FAST only.
+// not MODE_SLOW.
 template <typename T, int HV, bool SPMV, int NR, int NINB, bool SPLIT, int ROWS, bool STG = false,
           class PG = VmInterp>
 __device__ __forceinline__ void vm_step(
@@ -460,6 +462,7 @@ __device__ __forceinline__ void vm_step(
   typedef typename GVec<T, GS>::type gvec;
   typedef T vecA __attribute__((ext_vector_type(V), aligned(sizeof(T))));
   const VmParams& Q = step_params<PG>(P);   // the stream descriptors
+  const bool split = mode == MODE_EDGE && split_lane<V, U>(vmask);
   // element e of a register lives in group e / GS, component e % GS
 #define RSET(a, e, x) { const int g_ = (e) / GS; \
     if (g_ == 0) gset<T, GS>(R0[a], (e) % GS, x); else if (g_ == 1) gset<T, GS>(R1[a], (e) % GS, x); \
@@ -483,9 +486,12 @@ __device__ __forceinline__ void vm_step(
         const T* b = (const T*)Q.in[a].base;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const vecA w = *(const vecA*)(b + (row0 + u) * Q.in[a].s_row + c0);
+          // (a tile across the right edge: as in MODE_EDGE below)
+          const unsigned m = row_mask<V>(vmask, u);
+          const int sh = split ? edge_shift<V>(m) : 0;
+          const vecA w = *(const vecA*)(m != 0 ? b + (row0 + u) * Q.in[a].s_row + c0 + sh : b);
 #pragma unroll
-          for (int v = 0; v < V; ++v) RSET(a, u * V + v, w[v]);
+          for (int v = 0; v < V; ++v) RSET(a, u * V + v, (edge_elem<T, V>(w, sh, v)));
         }
       }
     }
@@ -538,7 +544,9 @@ __device__ __forceinline__ void vm_step(
     // every stream of the bucket, padding slots from a zero page, in flight
     // before the first wait (a compiled pass loads its own streams only)
     T Ls[NINB][E];
-    const bool split = mode == MODE_EDGE && split_lane<V, U>(vmask);
+    int sh[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) sh[u] = split ? edge_shift<V>(row_mask<V>(vmask, u)) : 0;
 #pragma unroll
     for (int a = 0; a < NINB; ++a) {
       if (PG::COMPILED && a >= n_in_of<PG>(P)) break;
@@ -555,7 +563,7 @@ __device__ __forceinline__ void vm_step(
           continue;
         }
         const T* p = b + (row0 + u) * Q.in[a].s_row + cc;
-        if (mode == MODE_EDGE) p = m != 0 && Q.in[a].s_col != 0 ? p + edge_shift<V>(m) : b;
+        if (mode == MODE_EDGE) p = m != 0 && Q.in[a].s_col != 0 ? p + sh[u] : b;
         const vecA w = *(const vecA*)p;
 #pragma unroll
         for (int v = 0; v < V; ++v) Ls[a][u * V + v] = w[v];
@@ -568,12 +576,11 @@ __device__ __forceinline__ void vm_step(
         if (PG::COMPILED && PG::bcol[a]) continue;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const int sh = edge_shift<V>(row_mask<V>(vmask, u));
           vecA w;
 #pragma unroll
           for (int v = 0; v < V; ++v) w[v] = Ls[a][u * V + v];
 #pragma unroll
-          for (int v = 0; v < V; ++v) Ls[a][u * V + v] = edge_elem<T, V>(w, sh, v);
+          for (int v = 0; v < V; ++v) Ls[a][u * V + v] = edge_elem<T, V>(w, sh[u], v);
         }
       }
     }
@@ -679,8 +686,13 @@ __device__ __forceinline__ void vm_step(
           else if (mode == MODE_FAST) *(vecA*)(b + (row0 + u) * sr + c0) = w;
           else {
             const unsigned m = row_mask<V>(vmask, u);
-            if (m == (1u << V) - 1) *(vecA*)(b + (row0 + u) * sr + c0) = w;
-            else if (m != 0) {
+            // (an edge step of whole vectors looks at no single elements:
+            // three interpreted sweeps of a 2500^2 grid 292 -> 270 us)
+            if (!split) {
+              if (m != 0) *(vecA*)(b + (row0 + u) * sr + c0) = w;
+            } else if (m == (1u << V) - 1) {
+              *(vecA*)(b + (row0 + u) * sr + c0) = w;
+            } else if (m != 0) {
 #pragma unroll
               for (int v = 0; v < V; ++v)
                 if ((m >> v) & 1) b[(row0 + u) * sr + c0 + v] = w[v];
@@ -889,14 +901,18 @@ template <typename T, int NW, int MAXCH> __device__ __forceinline__ void fin_sum
   }
 }
 
-// Stencil staging: an interior tile of a pass whose input streams include
+// Stencil staging: a tile of 32 rows of a pass whose input streams include
 // shifted views of one store (the stencil of section 2: five offset views of
 // one grid).  The tile's rows are processed in chunks of ST_RCH; for each
 // chunk the wave loads the window's ST_RCH + 2 rows (TW + 2 columns) once,
 // with 16-byte loads all in flight together, into its LDS slice, and every
 // staged stream of every step then reads its shifted values from LDS
 // instead of fetching them again from L2.  Other streams load as usual.
-// The op list runs unchanged on the same values, so the bits are the same.
+// The last strip's tiles are staged like the others: unstaged, they took
+// longest, in a grid of one or two waves per SIMD the whole launch waited for
+// them, and in a larger one they held a block's LDS (four compiled sweeps of
+// a 4099^2 grid 609 -> 576 us, three of a 2500^2 one 206 -> 165, interpreted
+// 292 -> 257).  The op list runs unchanged on the same values, so the bits are the same.
 constexpr int st_pitch(int tw, int es) { return tw + 16 / es; }
 
 template <typename T, int HV, bool SPMV, int NR, int NINB, int ROWS, class PG>
@@ -938,6 +954,16 @@ __device__ __forceinline__ void vm_stencil_tile(
   // two buffers the next chunk is staged while the current one is computed.
   __builtin_amdgcn_s_waitcnt(0);   // earlier LDS reads of this slice are complete
   stage(0);
+  // the tile's columns (a strip across the right edge: the window's rest is
+  // whatever follows in the store, never stored nor added)
+  unsigned vmask = (1u << E) - 1;
+  int mode = MODE_FAST;
+  if (cbase + TW > P.cols) {
+    mode = MODE_EDGE;
+    vmask = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) vmask |= (c0 + e % V < P.cols ? 1u : 0u) << e;
+  }
   for (int c = 0; c < NCH; ++c) {
     if constexpr (ST_NBUF > 1) {
       if (c + 1 < NCH) {
@@ -958,8 +984,7 @@ __device__ __forceinline__ void vm_stencil_tile(
     for (int q = 0; q < ST_RCH; q += U)
       vm_step<T, HV, SPMV, NR, NINB, false, ROWS, true, PG>(P, R0, R1, R2, R3, G, L,
                                                                tr * RED_TH + (int64_t)c * ST_RCH + q, c0,
-                                                               (1u << E) - 1, MODE_FAST, false, 0, nullptr, nullptr,
-                                                               cur, q, cbase);
+                                                               vmask, mode, false, 0, nullptr, nullptr, cur, q, cbase);
     if constexpr (ST_NBUF == 1)
       if (c + 1 < NCH) {
         __builtin_amdgcn_s_waitcnt(0);
@@ -1109,9 +1134,9 @@ void vm_kernel(const VmParams P) {
     bool have = false;  // L already holds this step's values (prefetched)
     bool staged = false;
     if constexpr (STEN && !SPMV && HV == 0) {
-      // stencil passes: a whole interior tile whose staged window lies in
+      // stencil passes: a tile of 32 whole rows whose staged window lies in
       // the store goes through LDS (vm_stencil_tile)
-      staged = split == 1 && P.st_n > 0 && P.unit_cols && (tr + 1) * RED_TH <= P.rows && cbase + TW <= P.cols &&
+      staged = split == 1 && P.st_n > 0 && P.lin_cols && P.unit_cols && (tr + 1) * RED_TH <= P.rows &&
                ((tr + 1) * RED_TH + 1) * P.st_srow + cbase + TW + 16 / (int)sizeof(T) <= P.st_lim;
       if (staged) vm_stencil_tile<T, HV, SPMV, NR, NINB, ROWS, PG>(P, R0, R1, R2, R3, G, L, tr, cbase, c0, wib);
     }

@@ -7,6 +7,7 @@ import pytest
 
 import paper_2406_18109_amd as dfx
 import synth
+import test_gpu_stencil as st
 from gpu_util import note, upload
 
 pytestmark = pytest.mark.gpu
@@ -55,3 +56,22 @@ def test_ragged_rows_and_broadcasts(dtype, off, C, monkeypatch):
         y, s = _run(dtype, R, C, off, jit, True, monkeypatch, (A, mu, w))
         assert np.array_equal(y, ey), jit
         assert np.array_equal(s, ref[1]), jit
+
+
+@pytest.mark.parametrize("make", [st._five_point, st._diagonal, st._horizontal])
+@pytest.mark.parametrize("shape", [(66, 131), (67, 259), (66, 257), (99, 5), (34, 388), (130, 130)])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("jit,coop", [(0, "0"), (2, "0"), (0, "1"), (2, "1")])
+def test_stencil_strip_across_the_right_edge(make, shape, dtype, jit, coop, monkeypatch):
+    """Staged tiles whose last strip is 1, 2, 3, ... columns wide, with a stream
+    that is not staged; and the same passes with a block for every tile."""
+    tasks, outs, temps = make(shape)
+    n = shape[0] * shape[1]
+    G = synth.uniform(17, 0, n, 0.5, 2.0).reshape(shape)
+    H = synth.uniform(17, 1, n, 0.5, 2.0).reshape(shape)
+    want = st._run_gpu(tasks, outs, temps, G, H, dtype, False)
+    monkeypatch.setenv("DFX_COOP", coop)
+    monkeypatch.setattr(st, "ctx", lambda fuse, window: dfx.Context(device=0, window_size=window, fuse=fuse, jit=jit))
+    got = st._run_gpu(tasks, outs, temps, G, H, dtype, True)
+    for k in outs:
+        np.testing.assert_array_equal(got[k], want[k], err_msg=k)
