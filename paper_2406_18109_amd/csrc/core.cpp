@@ -1492,15 +1492,22 @@ static int staged_streams(const PassPlan& p, size_t n_stores);
 //     7814 -> 7110, 380 cubed (13397) 16950 -> 15627.  A lone tile of one
 //     reduction stays with red_split, which spreads it over several blocks
 //     (CG 64: 209 against 232 us).
+//   stencil-staged passes (three Jacobi sweeps; a block reads the shifted
+//     views from L2 instead of staging them, which pays while the chip is not
+//     full): interpreted 400^2 (52 tiles) 161 -> 99 us, 2000^2 (1008) 225 ->
+//     205, 2500^2 (1580) 258 -> 293; compiled 400^2 113 -> 98, 1000^2 (256)
+//     113 -> 108, 2000^2 118 -> 147.
 // Two reductions are what 64 KB of LDS hold.  Above NOALLOC_BLOCKS tiles the
 // block sums would no longer fit the fixed scratch.  DFX_COOP=0 turns it off.
 constexpr int64_t COOP_VM_TILES = 512, COOP_VM_SPMV_TILES = 1024;
+constexpr int64_t COOP_STENCIL_TILES = 512, COOP_VM_STENCIL_TILES = 1024;
 static bool coop_pass(const PassPlan& p, bool compiled) {
   const char* e = std::getenv("DFX_COOP");
   if (e && e[0] == '0') return false;
   if (p.kind == 2 || p.tier != TIER_ARITH || p.red_cstore.empty() || p.red_cstore.size() > 2 || p.ins.size() > 6 ||
-      !p.unit_cols || p.n_tiles < 1 || staged_streams(p, SIZE_MAX) > 0)
+      !p.unit_cols || p.n_tiles < 1)
     return false;
+  if (staged_streams(p, SIZE_MAX) > 0) return p.n_tiles <= (compiled ? COOP_STENCIL_TILES : COOP_VM_STENCIL_TILES);
   if (!compiled) return p.n_tiles <= (p.kind == 1 ? COOP_VM_SPMV_TILES : COOP_VM_TILES);
   return (p.n_tiles > 1 || p.red_cstore.size() > 1) && p.n_tiles <= NOALLOC_BLOCKS;
 }
@@ -1767,6 +1774,7 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
     if (fn) P.lin_cols = lin_cols(p) && edge_ok(p);
   }
   const bool coop = coop_pass(p, fn != nullptr);
+  if (coop) P.st_n = 0;   // (it reads every stream as it is)
   // column shift (aligned output vectors), then row split, of passes
   // without reductions; either changes the launch shape only
   const int cs_shift = coop ? 0 : fn && ra_shift > 0 ? ra_shift : col_shift_for(p, P, es);
