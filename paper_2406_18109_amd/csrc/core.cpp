@@ -1476,7 +1476,7 @@ static int lin_cols(const PassPlan& p) {
 static int staged_streams(const PassPlan& p, size_t n_stores);
 
 // Whether a pass runs with a block of 16 waves for every tile (coop_kernel).
-// A reducing pass cannot split its rows over blocks (a tile's sum is one
+// Reducing passes: such a pass cannot split its rows over blocks (a tile's sum is one
 // ordered chain), so with a wave per tile it has as many waves as tiles and
 // is bound by that wave's walk over 32 rows.  Measured (graph replay of 8
 // iterations, one wave per tile against a block per tile; 64 to 300 are
@@ -1497,16 +1497,25 @@ static int staged_streams(const PassPlan& p, size_t n_stores);
 //     full): interpreted 400^2 (52 tiles) 161 -> 99 us, 2000^2 (1008) 225 ->
 //     205, 2500^2 (1580) 258 -> 293; compiled 400^2 113 -> 98, 1000^2 (256)
 //     113 -> 108, 2000^2 118 -> 147.
+//   SpMV passes without reductions (their rows can be split over blocks, so
+//     only the work inside a block differs: two rows of vectors per wave
+//     against rows staged through LDS): compiled, multigrid V-cycles over
+//     511^2 unknowns (64 tiles on the finest level) 2139 -> 2216 us, 1023^2
+//     (256) 3064 -> 2912, 2047^2 3096 -> 2910, 4095^2 8525 -> 7750;
+//     interpreted 1023^2 3693 -> 3587 but 2047^2 3440 -> 3471.
 // Two reductions are what 64 KB of LDS hold.  Above NOALLOC_BLOCKS tiles the
 // block sums would no longer fit the fixed scratch.  DFX_COOP=0 turns it off.
 constexpr int64_t COOP_VM_TILES = 512, COOP_VM_SPMV_TILES = 1024;
 constexpr int64_t COOP_STENCIL_TILES = 512, COOP_VM_STENCIL_TILES = 1024;
+constexpr int64_t COOP_ROWS_MIN_TILES = 256;
 static bool coop_pass(const PassPlan& p, bool compiled) {
   const char* e = std::getenv("DFX_COOP");
   if (e && e[0] == '0') return false;
-  if (p.kind == 2 || p.tier != TIER_ARITH || p.red_cstore.empty() || p.red_cstore.size() > 2 || p.ins.size() > 6 ||
-      !p.unit_cols || p.n_tiles < 1)
+  if (p.kind == 2 || p.tier != TIER_ARITH || p.red_cstore.size() > 2 || p.ins.size() > 6 || !p.unit_cols ||
+      p.n_tiles < 1)
     return false;
+  if (p.red_cstore.empty())
+    return compiled && p.kind == 1 && p.n_tiles >= COOP_ROWS_MIN_TILES && p.n_tiles <= NOALLOC_BLOCKS;
   if (staged_streams(p, SIZE_MAX) > 0) return p.n_tiles <= (compiled ? COOP_STENCIL_TILES : COOP_VM_STENCIL_TILES);
   if (!compiled) return p.n_tiles <= (p.kind == 1 ? COOP_VM_SPMV_TILES : COOP_VM_TILES);
   return (p.n_tiles > 1 || p.red_cstore.size() > 1) && p.n_tiles <= NOALLOC_BLOCKS;

@@ -148,3 +148,28 @@ def test_2d_sum_with_a_block_per_tile(shape, jit, monkeypatch):
         c.close()
     for a, b in zip(res[1], res[0]):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("dtype,n", [("f64", 255 * 4096 + 1), ("f64", 256 * 4096), ("f32", 255 * 8192 + 70)])
+def test_large_spmv_with_a_block_per_tile(dtype, n, monkeypatch):
+    """An SpMV without reductions over 256 tiles, its last one partial: rows of
+    0 to 11 entries, fused with an axpy, compiled."""
+    rng = np.random.default_rng(5)
+    rp = np.concatenate([[0], np.cumsum(rng.integers(0, 12, n))]).astype(np.int32)
+    col = rng.integers(0, n, rp[-1]).astype(np.int32)
+    npdt = np.float64 if dtype == "f64" else np.float32
+    val, x = rng.uniform(-1, 1, rp[-1]).astype(npdt), rng.uniform(-1, 1, n).astype(npdt)
+    res = []
+    for coop in ("0", "1"):
+        monkeypatch.setenv("DFX_COOP", coop)
+        c = dfx.Context(device=0, window_size=4, jit=2)
+        h = [upload(c, a) for a in (rp, col, val, x)]
+        y, r, s = c.store_create([n], dtype), upload(c, x), upload(c, np.asarray(0.5, npdt))
+        N, T, img = c.part_none(), c.part_tiling([n]), c.part_image(h[1], c.part_none())
+        c.submit("spmv_csr", [1], [(h[0], N, "R"), (h[1], N, "R"), (h[2], N, "R"), (h[3], img, "R"), (y, T, "W")])
+        c.submit("axpy", [1], [(s, N, "R"), (y, T, "R"), (r, T, "RW")], (-1.0,))
+        c.flush()
+        res.append((c.store_read(y, [n], dtype), c.store_read(r, [n], dtype)))
+        c.close()
+    for a, b in zip(*res):
+        np.testing.assert_array_equal(b, a)
