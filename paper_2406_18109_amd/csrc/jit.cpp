@@ -292,8 +292,11 @@ JitVariant jit_variant(int is_f64, int tier, int n_in, int spmv, int st_n, int r
   v.sten = (tier == TIER_ARITH && !spmv && st_n > 0 && v.nb != 2) ? 1 : 0;
   const bool plain = !spmv && !v.sten;
   // transcendental passes: two rows per step in FP64 (Black-Scholes over
-  // 2^26 options 0.793 against 0.807 ms with one), one in FP32 (0.361
-  // against 0.368 ms with two)
+  // 2^26 options 0.793 against 0.807 ms with one), one in FP32 (the same
+  // time as two, fewer registers).  They do not load the next step during
+  // this one: the waves resident hide the loads, and the registers held for
+  // them cost some (2^26 FP32 options 298 against 286.5 us, 50000003 216
+  // against 205.5; FP64 717 against 692)
   v.rows = plain ? (tier == TIER_ARITH ? (rows == 1 ? 1 : 0) : (is_f64 ? 2 : 1)) : 0;
   v.waves = spmv ? 4 : 2;
   if (plain) {
@@ -302,10 +305,6 @@ JitVariant jit_variant(int is_f64, int tier, int n_in, int spmv, int st_n, int r
     const char* w = std::getenv("DFX_JIT_WAVES");
     if (w && w[0] >= '1' && w[0] <= '8' && !w[1]) v.waves = w[0] - '0';
   }
-  // transcendental FP32 passes software-pipeline their loads (Black-Scholes
-  // FP32: 0.389 against 0.406 ms); FP64 ones do not (0.856 against 0.846 ms)
-  const char* pf = std::getenv("DFX_JIT_PF");
-  v.heavy_pf = (pf && (pf[0] == '0' || pf[0] == '1') && !pf[1]) ? pf[0] - '0' : (v.hv > 0 && !v.is_f64 ? 1 : 0);
   // parameters reloaded at every step: yes, except in stencil-staged and
   // realigning passes (set in jit_source), whose streaming steps measured
   // faster with them kept live (the 8192^2 Jacobi sweep 0.4443 against
@@ -322,7 +321,6 @@ std::string jit_source(const JitVariant& v, const JitProgram& g, std::string* na
   s += std::string("#include \"") + (v.coop ? "coop_exec.h" : "vm_exec.h") + "\"\n\nnamespace dfx {\n\nstruct JitPass {\n";
   s += "  static constexpr bool COMPILED = true;\n";
   s += "  static constexpr int WAVES = " + std::to_string(v.waves) + ";\n";
-  s += std::string("  static constexpr bool HEAVY_PF = ") + (v.heavy_pf ? "true" : "false") + ";\n";
   s += "  static constexpr int N_IN = " + std::to_string(g.n_in) + ", N_OUT = " + std::to_string(g.n_out) + ";\n";
   bool realigns = false;
   for (int32_t d : g.realign) realigns = realigns || d != 0;

@@ -39,7 +39,6 @@ struct JitVariant {
   int sten = 0;    // stencil staging variant
   int coop = 0;    // a block of this many waves per tile (coop_kernel), 0: vm_kernel
   int waves = 2;   // waves-per-SIMD target given to the compiler
-  int heavy_pf = 0; // transcendental pass: load the next step during this one
   int reload = -1;  // parameters reloaded at every step (step_params): 1, 0, -1 the default rule
 };
 
@@ -62,9 +61,8 @@ struct JitEntry;
 // prologue `spmv`, `st_n` staged streams and the planner's rows per step:
 // the interpreter's, except that FP32 transcendental passes take one row
 // per step (their straight-line code keeps few registers that way, so more
-// waves are resident) and prefetch the next step's loads, and FP64 ones
-// take two.  DFX_JIT_ROWS (0, 1 or 2) and DFX_JIT_WAVES override the
-// choice for non-SpMV, unstaged passes, DFX_JIT_PF (0 or 1) the prefetch,
+// waves are resident) and FP64 ones take two.  DFX_JIT_ROWS (0, 1 or 2) and
+// DFX_JIT_WAVES override the choice for non-SpMV, unstaged passes,
 // DFX_JIT_RELOAD (0 or 1) whether parameters are reloaded at every step.
 JitVariant jit_variant(int is_f64, int tier, int n_in, int spmv, int st_n, int rows);
 

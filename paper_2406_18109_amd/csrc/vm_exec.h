@@ -170,15 +170,13 @@ __device__ __forceinline__ void vm_instr(typename GVec<T, GS>::type (&R0)[NR], t
 // (P.code, P.out_reg, P.bc_reg, P.st_on/st_dr/st_dc).  A compiled pass's
 // program type, generated by the host for that one pass, has COMPILED true,
 // its output and broadcast register maps and its stencil staging map as
-// constants, its waves-per-SIMD target (WAVES), whether a transcendental
-// pass software-pipelines its loads (HEAVY_PF) and a run() that calls
+// constants, its waves-per-SIMD target (WAVES) and a run() that calls
 // vm_instr for each instruction in order.
 struct VmInterp {
   static constexpr bool COMPILED = false;
   static constexpr int N_IN = 0, N_OUT = 0;   // (compiled passes: the pass's stream counts)
   static constexpr bool RELOAD = false;       // (compiled passes: parameters reloaded per step)
   static constexpr int WAVES = 1;
-  static constexpr bool HEAVY_PF = false;   // transcendental passes prefetch the next step
   static constexpr int out_reg[VM_MAXOUT] = {};
   static constexpr int bc_reg[VM_MAXBC] = {};
   static constexpr int st_on[VM_MAXIN] = {}, st_dr[VM_MAXIN] = {}, st_dc[VM_MAXIN] = {};
@@ -1100,23 +1098,21 @@ void vm_kernel(const VmParams P) {
   // Arithmetic passes are stream-bound: their loads are software-pipelined
   // one step ahead inside a tile (up to four streams: the wider bucket would
   // lose a wave of occupancy to the prefetch registers).  Transcendental
-  // passes are not (DFX_HEAVY_PF=1 pipelines them too: 2 % faster for
-  // Black-Scholes FP64 with the load buffer, but the buffer costs a wave).
+  // passes are not: their waves' arithmetic hides the loads, and the load
+  // buffer costs registers (compiled FP32 Black-Scholes over 2^26 options
+  // 298 us with it, 286.5 without).
 #ifndef DFX_PREFETCH_MAX_STREAMS
 #define DFX_PREFETCH_MAX_STREAMS 4
 #endif
-#ifndef DFX_HEAVY_PF
-#define DFX_HEAVY_PF 0
-#endif
-  constexpr bool PF = !SPMV && NINB <= DFX_PREFETCH_MAX_STREAMS && (!S::HEAVY || DFX_HEAVY_PF || PG::HEAVY_PF);
-  // FP32 transcendental kernels load through vm_load (padding slots
-  // skipped).  The FP64 ones load straight into the register file: without
+  constexpr bool PF = !SPMV && NINB <= DFX_PREFETCH_MAX_STREAMS && !S::HEAVY;
+  // Interpreted FP32 transcendental kernels load through vm_load (padding
+  // slots skipped).  The FP64 ones load straight into the register file: without
   // the separate load buffer they fit three waves per SIMD instead of two
   // (1.05 against 1.26 ms for Black-Scholes FP64 over 2^26 options).
 #ifndef DFX_HEAVY_SPLIT
 #define DFX_HEAVY_SPLIT (sizeof(T) == 4)
 #endif
-  constexpr bool SPLIT = PF || (S::HEAVY && !SPMV && DFX_HEAVY_SPLIT);
+  constexpr bool SPLIT = PF || (S::HEAVY && !SPMV && !PG::COMPILED && DFX_HEAVY_SPLIT);
   T L[NINB][E];
   for (int64_t t = t_begin; t < t_end; ++t) {
     const int64_t tr = t / P.strips;
