@@ -337,7 +337,7 @@ std::string jit_source(const JitVariant& v, const JitProgram& g, std::string* na
   s += "  static constexpr int realign[VM_MAXIN] = " + int_list(g.realign, VM_MAXIN) + ";\n";
   s += "  static constexpr int N_RED = " + std::to_string(g.n_red) + ";\n";
   s += std::string("  static constexpr bool RSPLIT = ") + (g.rsplit ? "true" : "false") + ", FIN = " +
-       (g.fin ? "true" : "false") + ";\n";
+       (g.fin ? "true" : "false") + ", LINE = " + (g.line ? "true" : "false") + ";\n";
   s += "  static constexpr int bcol[VM_MAXIN] = " + int_list(g.bcol, VM_MAXIN) + ";\n";
   s += "  template <typename T, int HV, int NR, int NG, int GS, int E>\n";
   s += "  static __device__ __forceinline__ void run(typename GVec<T, GS>::type (&R0)[NR],\n"

@@ -48,6 +48,7 @@ struct JitProgram {
   int n_red = 0;             // reductions
   bool rsplit = false;       // may run under red_split
   bool fin = false;          // may be one block that reduces an earlier pass's block sums
+  bool line = false;         // one-dimensional and transcendental: ragged steps go element by element
   std::vector<VmInstr> code;
   std::vector<int32_t> out_reg, bc_reg;
   std::vector<int32_t> st_on, st_dr, st_dc;   // stencil staging map (empty: none)

@@ -193,6 +193,7 @@ struct VmInterp {
   // a pass without reductions made 5e7 FP32 options 227 instead of 216 us).
   static constexpr int N_RED = 0;
   static constexpr bool RSPLIT = false, FIN = false;
+  static constexpr bool LINE = false;   // (compiled passes) ragged steps take MODE_SLOW, not MODE_EDGE
   template <typename T, int HV, int NR, int NG, int GS, int E>
   static __device__ __forceinline__ void run(typename GVec<T, GS>::type (&)[NR], typename GVec<T, GS>::type (&)[NR],
                                              typename GVec<T, GS>::type (&)[NR], typename GVec<T, GS>::type (&)[NR],
@@ -382,7 +383,7 @@ __device__ __forceinline__ void vm_load(const VmParams& P, T (&L)[NINB][E], int6
       return;
     }
   }
-  const bool split = mode == MODE_EDGE && split_lane<V, U>(vmask);
+  const bool split = !PG::LINE && mode == MODE_EDGE && split_lane<V, U>(vmask);
   int sh[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) sh[u] = split ? edge_shift<V>(row_mask<V>(vmask, u)) : 0;
@@ -460,7 +461,7 @@ __device__ __forceinline__ void vm_step(
   typedef typename GVec<T, GS>::type gvec;
   typedef T vecA __attribute__((ext_vector_type(V), aligned(sizeof(T))));
   const VmParams& Q = step_params<PG>(P);   // the stream descriptors
-  const bool split = mode == MODE_EDGE && split_lane<V, U>(vmask);
+  const bool split = !PG::LINE && mode == MODE_EDGE && split_lane<V, U>(vmask);
   // element e of a register lives in group e / GS, component e % GS
 #define RSET(a, e, x) { const int g_ = (e) / GS; \
     if (g_ == 0) gset<T, GS>(R0[a], (e) % GS, x); else if (g_ == 1) gset<T, GS>(R1[a], (e) % GS, x); \
@@ -1151,7 +1152,7 @@ void vm_kernel(const VmParams P) {
       int mode = MODE_FAST;
       unsigned vmask = (1u << E) - 1;
       if (!(DFX_C(lin_cols) && interior)) {
-        mode = DFX_C(lin_cols) ? MODE_EDGE : MODE_SLOW;
+        mode = DFX_C(lin_cols) && !PG::LINE ? MODE_EDGE : MODE_SLOW;
         vmask = 0;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
