@@ -1,5 +1,5 @@
 // A tile run by a whole block: the device side of the batched executor
-// (batch.hip) and of chained small passes (chain.hip).
+// (batch.hip) and of single passes of few tiles (coop_kernel).
 //
 // Where few tiles are in flight, one wave walking a tile's 32 rows is bound
 // by the latency of each row (an SpMV row alone is three dependent loads).
