@@ -1456,10 +1456,12 @@ static int row_split_for(const PassPlan& p, const VmParams& P) {
   return s;
 }
 
-// The vector modes need rows of at least one vector (the kernel's edge_shift).
-static bool edge_ok(const PassPlan& p) {
+// VmParams.lin_cols of a pass whose streams allow vectors: they need rows of
+// at least one (the kernel's edge_shift).
+static int lin_mode(const PassPlan& p, int col_shift) {
   const int64_t V = p.dtype == DFX_F64 ? Lanes<double>::V : Lanes<float>::V;
-  return (p.is1d ? p.n1d : p.cols) >= V;
+  const int64_t w = p.is1d ? p.n1d : p.cols;
+  return w < V ? 0 : w % V == 0 && !col_shift ? LIN_WHOLE : LIN_SPLIT;
 }
 
 // Whether the pass's steps take the vector modes when it runs compiled:
@@ -1687,7 +1689,6 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
   P.spmv = p.kind == 1;
   P.grid = p.grid;
   P.unit_cols = p.unit_cols;
-  P.lin_cols = p.unit_cols && edge_ok(p);
   P.rows = p.rows;
   P.cols = p.cols;
   P.n1d = p.n1d;
@@ -1783,13 +1784,13 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
     }
     if (p.jit && ra == p.realign && p.jit_coop == coop_pass(p, true))
       fn = jit_function(*p.jit, c.cfg.device, !c.capturing);
-    if (fn) P.lin_cols = lin_cols(p) && edge_ok(p);
   }
   const bool coop = coop_pass(p, fn != nullptr);
   if (coop) P.st_n = 0;   // (it reads every stream as it is)
   // column shift (aligned output vectors), then row split, of passes
   // without reductions; either changes the launch shape only
   const int cs_shift = coop ? 0 : fn && ra_shift > 0 ? ra_shift : col_shift_for(p, P, es);
+  P.lin_cols = (fn ? lin_cols(p) : p.unit_cols) ? lin_mode(p, cs_shift) : 0;
   if (const int cs = cs_shift; cs > 0) {
     const int64_t TWp = p.dtype == DFX_F64 ? Lanes<double>::TW : Lanes<float>::TW;
     const int64_t row_tiles = p.n_tiles / std::max<int64_t>(1, p.strips);

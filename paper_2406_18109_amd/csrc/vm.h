@@ -132,14 +132,18 @@ struct VmFinal {
 // earlier pass's VmFinal), at most FIN_MAX_CHUNKS chunks of FINAL_CHUNK.
 constexpr int FIN_MAX_CHUNKS = 64;
 
+// VmParams.lin_cols: whether a lane's vector may cross the space's edge, or
+// none does.
+enum { LIN_SPLIT = 1, LIN_WHOLE = 2 };
+
 struct VmParams {
   int32_t n_code, n_in, n_out, n_bc, n_red;
   int32_t is1d;         // 1: space of n1d elements cut into rows of TW
   int32_t spmv;         // 1: row result of y = A x lands in VM_SPMV_REG first
   int32_t grid;         // blocks launched
   int32_t unit_cols;    // every stream has column stride 1 (padding slots 0)
-  int32_t lin_cols;     // steps take the vector modes: unit_cols, or a compiled pass whose other
-                        // inputs have column stride 0 (a value per row)
+  int32_t lin_cols;     // not 0: steps take the vector modes (unit_cols, or a compiled pass whose other
+                        // inputs have column stride 0, a value per row)
   int64_t rows, cols;   // 2-D space; for 1-D: rows = ceil(n1d / TW), cols = TW
   int64_t n1d;
   int64_t n_tiles, strips;  // tiles, tiles per tile-row

@@ -200,27 +200,19 @@ struct VmInterp {
                                              VmState<T, NG, GS>&, unsigned) {}
 };
 
-enum StepMode { MODE_FAST = 0, MODE_EDGE = 1, MODE_SLOW = 2 };
+// (vm_step says what each does)
+enum StepMode { MODE_FAST = 0, MODE_EDGE = 1, MODE_SLOW = 2, MODE_WHOLE = 3 };
 
 // The valid elements of row u of a step.
 template <int V> __device__ __forceinline__ unsigned row_mask(const unsigned vmask, const int u) {
   return (vmask >> (u * V)) & ((1u << V) - 1);
 }
-// Whether some lane of the step has a row of which only part is valid.
-template <int V, int U> __device__ __forceinline__ bool split_lane(const unsigned vmask) {
-  bool s = false;
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const unsigned m = row_mask<V>(vmask, u);
-    s = s || (m != 0 && m != (1u << V) - 1);
-  }
-  return __ballot(s) != 0ull;
-}
-// Such a lane loads the vector that ends (or, across the space's left edge,
-// begins) at the boundary, so every edge step is one round of vector loads
-// like any other: edge_shift is that vector's offset from the lane's own
-// (valid elements m), edge_elem the lane's element v of it.  Rows are at
-// least V elements wide, so the vector stays inside the row.
+// A lane with a row of which only part is valid loads the vector that ends
+// (or, across the space's left edge, begins) at the boundary, so every edge
+// step is one round of vector loads like any other: edge_shift is that
+// vector's offset from the lane's own (valid elements m), edge_elem the lane's
+// element v of it.  Rows are at least V elements wide, so the vector stays
+// inside the row.
 template <int V> __device__ __forceinline__ int edge_shift(const unsigned m) {
   const int out = V - (int)__builtin_popcount(m);
   return m == 0 ? 0 : (m & 1) ? -out : out;
@@ -383,10 +375,13 @@ __device__ __forceinline__ void vm_load(const VmParams& P, T (&L)[NINB][E], int6
       return;
     }
   }
-  const bool split = !PG::LINE && mode == MODE_EDGE && split_lane<V, U>(vmask);
   int sh[U];
 #pragma unroll
-  for (int u = 0; u < U; ++u) sh[u] = split ? edge_shift<V>(row_mask<V>(vmask, u)) : 0;
+  for (int u = 0; u < U; ++u) sh[u] = 0;
+  if (mode == MODE_EDGE) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) sh[u] = edge_shift<V>(row_mask<V>(vmask, u));
+  }
 #pragma unroll
   for (int a = 0; a < NINB; ++a) {
     if (a >= n_in_of<PG>(P)) break;
@@ -401,38 +396,44 @@ __device__ __forceinline__ void vm_load(const VmParams& P, T (&L)[NINB][E], int6
         continue;
       }
       const T* p = b + (row0 + u) * Q.in[a].s_row + c0;
-      if (mode == MODE_EDGE) p = m != 0 ? p + sh[u] : b;
+      if (mode != MODE_FAST) p = m != 0 ? p + sh[u] : b;
       const vecA w = *(const vecA*)p;
 #pragma unroll
       for (int v = 0; v < V; ++v) L[a][u * V + v] = w[v];
     }
   }
-  if (split) {
+  // (elsewhere the step picks the elements: see vm_step)
+  if constexpr (PG::REALIGN)
+    if (mode == MODE_EDGE) {
 #pragma unroll
-    for (int a = 0; a < NINB; ++a) {
-      if (a >= n_in_of<PG>(P)) break;
-      if (PG::COMPILED && PG::bcol[a]) continue;
+      for (int a = 0; a < NINB; ++a) {
+        if (a >= n_in_of<PG>(P)) break;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        vecA w;
+        for (int u = 0; u < U; ++u) {
+          vecA w;
 #pragma unroll
-        for (int v = 0; v < V; ++v) w[v] = L[a][u * V + v];
+          for (int v = 0; v < V; ++v) w[v] = L[a][u * V + v];
 #pragma unroll
-        for (int v = 0; v < V; ++v) L[a][u * V + v] = edge_elem<T, V>(w, sh[u], v);
+          for (int v = 0; v < V; ++v) L[a][u * V + v] = edge_elem<T, V>(w, PG::bcol[a] ? 0 : sh[u], v);
+        }
       }
     }
-  }
 }
 
 // One step: U rows of the tile, V columns per lane.
 //   MODE_FAST : every slot of every lane valid, unit column strides (in a
 //               compiled pass also inputs of column stride 0: a value per
 //               row): vector loads of all streams issued back to back.
-//   MODE_EDGE : the same strides, some slots outside the space: the same
-//               vector loads, lanes outside pointed at the stream's first
-//               element, a lane across the boundary at the vector that ends
-//               there (edge_shift).  What is outside is never stored nor
-//               added.
+//   MODE_WHOLE: the same strides, some slots outside the space, every lane's
+//               vector inside or outside as a whole: the same vector loads,
+//               lanes outside pointed at the stream's first element.  What is
+//               outside is never stored nor added.
+//   MODE_EDGE : the same where a vector may cross the boundary: a lane across
+//               it loads the vector that ends there (edge_shift).  With the
+//               narrow tables' steps in one mode for both, interpreted,
+//               40000 x 100 doubles times a constant took 29.7 us instead of
+//               25.1 (four streams added 39.6 and 34.9), and every step of a
+//               small pass paid too (1048576 doubles 9.2 and 8.6).
 //   MODE_SLOW : per-element masked accesses, one stream at a time.
 // Slots n_in..NINB-1 of the bucket read a 4 KB zero page in the vector modes.
 // With SPLIT the caller has instead issued the step's loads into L (see
@@ -461,7 +462,12 @@ __device__ __forceinline__ void vm_step(
   typedef typename GVec<T, GS>::type gvec;
   typedef T vecA __attribute__((ext_vector_type(V), aligned(sizeof(T))));
   const VmParams& Q = step_params<PG>(P);   // the stream descriptors
-  const bool split = !PG::LINE && mode == MODE_EDGE && split_lane<V, U>(vmask);
+  const bool split = !PG::LINE && mode == MODE_EDGE;
+  // (whether whole vectors' stores have a branch of their own; the
+  // interpreter's kernels of floats other than the four-stream one are better
+  // without: a 4096^2 float copy 35.2 against 36.6 us, 40000 x 100 floats of
+  // four streams 39.9 with it and 41.0 without)
+  constexpr bool WHOLE_FIRST = sizeof(T) == 8 || (NINB == 4 && !HEAVY && !STG);
   // element e of a register lives in group e / GS, component e % GS
 #define RSET(a, e, x) { const int g_ = (e) / GS; \
     if (g_ == 0) gset<T, GS>(R0[a], (e) % GS, x); else if (g_ == 1) gset<T, GS>(R1[a], (e) % GS, x); \
@@ -485,22 +491,49 @@ __device__ __forceinline__ void vm_step(
         const T* b = (const T*)Q.in[a].base;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          // (a tile across the right edge: as in MODE_EDGE below)
+          // (a tile across the right edge: as an edge step)
           const unsigned m = row_mask<V>(vmask, u);
-          const int sh = split ? edge_shift<V>(m) : 0;
-          const vecA w = *(const vecA*)(m != 0 ? b + (row0 + u) * Q.in[a].s_row + c0 + sh : b);
+          const T* p = b + (row0 + u) * Q.in[a].s_row + c0;
+          if (mode != MODE_FAST) p = m != 0 ? p + (split ? edge_shift<V>(m) : 0) : b;
+          vecA w = *(const vecA*)p;
+          if (split) {
+            const vecA w0 = w;
 #pragma unroll
-          for (int v = 0; v < V; ++v) RSET(a, u * V + v, (edge_elem<T, V>(w, sh, v)));
+            for (int v = 0; v < V; ++v) w[v] = edge_elem<T, V>(w0, edge_shift<V>(m), v);
+          }
+#pragma unroll
+          for (int v = 0; v < V; ++v) RSET(a, u * V + v, w[v]);
         }
       }
     }
   } else if (mode != MODE_SLOW && SPLIT) {
     // issued by the caller (or prefetched by the previous step) into L
+    // (a lane across the edge picks its elements here: done in place in L, it
+    // put copies and a wait into every step, 1048576 doubles times a constant
+    // 9.2 us instead of 8.6; realigning passes, which move L about anyway, are
+    // better in place, a copy into the interior of a 6000^2 grid 128.2 against
+    // 141.6 us)
+    if (split && !PG::REALIGN) {
 #pragma unroll
-    for (int a = 0; a < NINB; ++a) {
-      if (a >= n_in_of<PG>(P)) break;
+      for (int a = 0; a < NINB; ++a) {
+        if (a >= n_in_of<PG>(P)) break;
 #pragma unroll
-      for (int e = 0; e < E; ++e) RSET(a, e, L[a][e]);
+        for (int u = 0; u < U; ++u) {
+          const int sh = PG::COMPILED && PG::bcol[a] ? 0 : edge_shift<V>(row_mask<V>(vmask, u));
+          vecA w;
+#pragma unroll
+          for (int v = 0; v < V; ++v) w[v] = L[a][u * V + v];
+#pragma unroll
+          for (int v = 0; v < V; ++v) RSET(a, u * V + v, (edge_elem<T, V>(w, sh, v)));
+        }
+      }
+    } else {
+#pragma unroll
+      for (int a = 0; a < NINB; ++a) {
+        if (a >= n_in_of<PG>(P)) break;
+#pragma unroll
+        for (int e = 0; e < E; ++e) RSET(a, e, L[a][e]);
+      }
     }
     if (pf_next) vm_load<T, V, U, E, NINB, PG>(P, L, next_row0, c0, (1u << E) - 1, MODE_FAST, cbase);
   } else if (PG::COMPILED && mode == MODE_FAST) {
@@ -545,7 +578,11 @@ __device__ __forceinline__ void vm_step(
     T Ls[NINB][E];
     int sh[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) sh[u] = split ? edge_shift<V>(row_mask<V>(vmask, u)) : 0;
+    for (int u = 0; u < U; ++u) sh[u] = 0;
+    if (split) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) sh[u] = edge_shift<V>(row_mask<V>(vmask, u));
+    }
 #pragma unroll
     for (int a = 0; a < NINB; ++a) {
       if (PG::COMPILED && a >= n_in_of<PG>(P)) break;
@@ -562,7 +599,7 @@ __device__ __forceinline__ void vm_step(
           continue;
         }
         const T* p = b + (row0 + u) * Q.in[a].s_row + cc;
-        if (mode == MODE_EDGE) p = m != 0 && Q.in[a].s_col != 0 ? p + sh[u] : b;
+        if (mode != MODE_FAST) p = m != 0 && Q.in[a].s_col != 0 ? p + sh[u] : b;
         const vecA w = *(const vecA*)p;
 #pragma unroll
         for (int v = 0; v < V; ++v) Ls[a][u * V + v] = w[v];
@@ -685,9 +722,7 @@ __device__ __forceinline__ void vm_step(
           else if (mode == MODE_FAST) *(vecA*)(b + (row0 + u) * sr + c0) = w;
           else {
             const unsigned m = row_mask<V>(vmask, u);
-            // (an edge step of whole vectors looks at no single elements:
-            // three interpreted sweeps of a 2500^2 grid 292 -> 270 us)
-            if (!split) {
+            if (WHOLE_FIRST && mode == MODE_WHOLE) {
               if (m != 0) *(vecA*)(b + (row0 + u) * sr + c0) = w;
             } else if (m == (1u << V) - 1) {
               *(vecA*)(b + (row0 + u) * sr + c0) = w;
@@ -958,7 +993,7 @@ __device__ __forceinline__ void vm_stencil_tile(
   unsigned vmask = (1u << E) - 1;
   int mode = MODE_FAST;
   if (cbase + TW > P.cols) {
-    mode = MODE_EDGE;
+    mode = P.lin_cols == LIN_WHOLE ? MODE_WHOLE : MODE_EDGE;
     vmask = 0;
 #pragma unroll
     for (int e = 0; e < E; ++e) vmask |= (c0 + e % V < P.cols ? 1u : 0u) << e;
@@ -1152,7 +1187,7 @@ void vm_kernel(const VmParams P) {
       int mode = MODE_FAST;
       unsigned vmask = (1u << E) - 1;
       if (!(DFX_C(lin_cols) && interior)) {
-        mode = DFX_C(lin_cols) && !PG::LINE ? MODE_EDGE : MODE_SLOW;
+        mode = PG::LINE || !DFX_C(lin_cols) ? MODE_SLOW : DFX_C(lin_cols) == LIN_WHOLE ? MODE_WHOLE : MODE_EDGE;
         vmask = 0;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
