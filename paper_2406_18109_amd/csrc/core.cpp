@@ -1415,13 +1415,16 @@ static int realign_for(const PassPlan& p, const VmParams& P, size_t es, std::vec
   return any ? (int)m : 0;
 }
 
-// Dynamic LDS that a realigning pass's launch asks for and does not use: with
-// it four blocks fit a compute unit.  Such a pass holds few registers and
+// Dynamic LDS that a large realigning pass's launch asks for and does not use:
+// with it four blocks fit a compute unit.  Such a pass holds few registers and
 // would have eight waves per SIMD resident, whose rows in flight are spread
-// over more of memory than streams well (four sweeps of an 8192^2 Jacobi
-// grid, with its copy at eight waves 2117 us, six 2087, four 2072, three
-// 2085).
+// over more of memory than streams well: a scaled copy into the interior of a
+// grid of doubles with four blocks against all that fit, 16384^2 1103 against
+// 1135 us, 8192^2 202 against 217, 7000^2 157 against 163.  Where much of the
+// data stays in the last-level cache every wave is wanted: 6000^2 (576 MB)
+// 131.8 against 127.7, 4096^2 61.3 against 48.4, 3000^2 33.6 against 27.1.
 constexpr size_t REALIGN_LDS = 39 * 1024;
+constexpr int64_t REALIGN_LDS_BYTES = (int64_t)640 << 20;   // of the pass's streams
 // The same for a compiled stencil-staged pass: two blocks, so that eight
 // waves stream beside one another, not the twelve its buffers would allow
 // (four sweeps of an 8192^2 grid 2060 against 2117 us, of a 4099^2 one 610
@@ -1875,7 +1878,7 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
   } else if (fn) {
     const JitVariant v = jit_variant(p.dtype == DFX_F64, p.tier, P.n_in, P.spmv, P.st_n, rows);
     size_t lds = coop ? coop_lds(P.n_red, P.spmv != 0) : vm_dyn_lds_bytes(P, v.sten != 0);
-    if (ra_shift > 0) lds = std::max(lds, REALIGN_LDS);
+    if (ra_shift > 0 && p.alg_bytes >= REALIGN_LDS_BYTES) lds = std::max(lds, REALIGN_LDS);
     if (v.sten) lds = std::max(lds, STENCIL_LDS);
     void* args[] = {(void*)&P};
     e = (int)hipModuleLaunchKernel(fn, (unsigned)P.grid, 1, 1, coop ? COOP_BLOCK : BLOCK, 1, 1, (unsigned)lds, c.stream,
