@@ -348,8 +348,9 @@ int dfx_group_get(dfx_ctx* ctx, int64_t i, dfx_group_info* out);
  * restart = 0 resumes streams paused by round_limit (> 0: a stream pauses
  * after that many body repetitions in one launch) and leaves finished ones.
  * dfx_batch_wait synchronises and reads the stream states back; it returns
- * DFX_EHIP if the kernel's stall detector ended the launch (no pass of any
- * stream completed for several seconds).  Errors: dfx_batch_last_error. */
+ * DFX_EHIP if the launch ended with a stream neither done nor paused (some
+ * part of the device ran none of its streams).  Errors:
+ * dfx_batch_last_error. */
 typedef struct dfx_batch dfx_batch;
 enum { DFX_BATCH_RUNNING = 0, DFX_BATCH_DONE = 1, DFX_BATCH_PAUSED = 2 };
 int dfx_batch_create(int32_t device, void* stream, dfx_batch** out);

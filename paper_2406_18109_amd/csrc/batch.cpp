@@ -340,23 +340,22 @@ int dfx_batch_wait(dfx_batch* b) {
           hipSuccess ||
       hipMemcpy(&b->ctl, b->d_ctl, sizeof(BatchCtl), hipMemcpyDeviceToHost) != hipSuccess)
     return bfail(b, DFX_EHIP, "batch state read-back");
-  for (int x = 0; x < b->n_xcd; ++x)
-    if (b->ctl.x[x].error) {
-      std::string m = "batch stopped: no pass completed for a long time (stall detector); XCD ids seen 0x";
-      char buf[512];
-      std::snprintf(buf, sizeof(buf), "%x; waves per XCD id:", b->ctl.xcc_seen);
+  if (!all_settled(b->ctl.x, (uint32_t)b->n_xcd)) {
+    std::string m = "batch stopped before every stream was done or paused; XCD ids seen 0x";
+    char buf[512];
+    std::snprintf(buf, sizeof(buf), "%x; waves per XCD id:", b->ctl.xcc_seen);
+    m += buf;
+    for (int k = 0; k < 16; ++k) {
+      std::snprintf(buf, sizeof(buf), " %u", b->ctl.waves[k]);
       m += buf;
-      for (int k = 0; k < 16; ++k) {
-        std::snprintf(buf, sizeof(buf), " %u", b->ctl.waves[k]);
-        m += buf;
-      }
-      for (int k = 0; k < b->n_xcd; ++k) {
-        std::snprintf(buf, sizeof(buf), "; xcd %d: %u streams, %u settled, %u passes, error %d", k,
-                      b->ctl.x[k].n_streams, b->ctl.x[k].n_settled, b->ctl.x[k].progress, b->ctl.x[k].error);
-        m += buf;
-      }
-      return bfail(b, DFX_EHIP, m);
     }
+    for (int k = 0; k < b->n_xcd; ++k) {
+      std::snprintf(buf, sizeof(buf), "; xcd %d: %u streams, %u settled, %u passes, error %d", k,
+                    b->ctl.x[k].n_streams, b->ctl.x[k].n_settled, b->ctl.x[k].progress, b->ctl.x[k].error);
+      m += buf;
+    }
+    return bfail(b, DFX_EHIP, m);
+  }
   return DFX_OK;
 }
 

@@ -27,9 +27,21 @@ struct XcdCtl {
   uint32_t n_streams;            // streams of this XCD
   uint32_t n_settled;            // of them, settled in this launch
   uint32_t progress;             // passes completed: the stall detector's clock
-  int32_t error;                 // 1: the stall detector fired
+  int32_t error;                 // 1: the stall detector fired (idle blocks left early)
   uint32_t first;                // (solve server) its first entry of the round's list
   uint32_t pad[59];
 };
+
+// Whether a launch settled every stream: after it, the one thing that says so.
+// An XCD that got no block sets no error, and the stall detector's error loses
+// nothing by itself: a block leaves on it only with nothing taken and nothing
+// to claim, and what is published later is carried on by the block that
+// publishes it.  (The detector's clock runs on while a shared GPU has another
+// process's work in the queue's place.)
+inline bool all_settled(const XcdCtl* x, uint32_t n_xcd) {
+  for (uint32_t k = 0; k < n_xcd; ++k)
+    if (x[k].n_settled != x[k].n_streams) return false;
+  return true;
+}
 
 }  // namespace dfx

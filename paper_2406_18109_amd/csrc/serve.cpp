@@ -119,6 +119,7 @@ struct Server {
   char* d_round = nullptr;          // [ServeRound | ServeClaim x max_slots | list x max_slots]
   char* h_round = nullptr;          // pinned staging; its ServeRound is read back
   int n_cu = 0;
+  bool by_phases = false;           // a persistent round left an XCD's solves unrun
   size_t item_cap = 0;
   Tuner tuner;
   dfx_serve_counters stats{};
@@ -293,6 +294,13 @@ static bool round_fits(int64_t fullest) {
   return fullest <= ROUND_MAX_TILES;
 }
 
+// Blocks of a persistent round: one per compute unit (any number runs every
+// solve of the XCDs it reaches; DFX_SERVE_BLOCKS=<n> sets it).
+static int round_blocks(const Server& S) {
+  const char* e = std::getenv("DFX_SERVE_BLOCKS");
+  return std::max(1, e ? std::min(std::atoi(e), S.n_cu) : S.n_cu);
+}
+
 // The round as one persistent launch.
 static int persistent_round(Server& S, int ipr, const std::vector<int> (&at)[MAX_XCD]) {
   const size_t ms = S.slots.size();
@@ -319,10 +327,28 @@ static int persistent_round(Server& S, int ipr, const std::vector<int> (&at)[MAX
   if (!e)
     e = launch_serve_round(S.d_solves, (ServeClaim*)(S.d_round + sizeof(ServeRound)),
                            (const int32_t*)(S.d_round + sizeof(ServeRound) + ms * sizeof(ServeClaim)),
-                           (ServeRound*)S.d_round, std::max(1, S.n_cu), S.stream);
+                           (ServeRound*)S.d_round, round_blocks(S), S.stream);
   if (!e) e = hipMemcpyAsync(S.h_round, S.d_round, sizeof(ServeRound), hipMemcpyDeviceToHost, S.stream);
   S.stats.launches += 1;
   return e;
+}
+
+// What a persistent round did, once it and its read-back are complete.  Solves
+// of an XCD that got no block are run by phase launches from the next round
+// on.  Returns false when the round broke off.
+static bool check_round(Server& S) {
+  const size_t ms = S.slots.size();
+  const ServeRound& R = *(const ServeRound*)S.h_round;
+  if (all_settled(R.x, R.n_xcd)) return true;
+  const ServeClaim* given = (const ServeClaim*)(S.h_round + sizeof(ServeRound));
+  const int32_t* list = (const int32_t*)(S.h_round + sizeof(ServeRound) + ms * sizeof(ServeClaim));
+  std::vector<ServeClaim> now(ms);
+  if (hipMemcpy(now.data(), S.d_round + sizeof(ServeRound), ms * sizeof(ServeClaim), hipMemcpyDeviceToHost) !=
+          hipSuccess ||
+      round_end(R, list, given, now.data()) == ROUND_BROKEN)
+    return false;
+  S.by_phases = true;
+  return true;
 }
 
 static void scheduler(Server* Sp) {
@@ -367,7 +393,7 @@ static void scheduler(Server* Sp) {
     for (auto& sl : S.slots)
       if (sl.used) { n_all += sl.n_tiles; if (sl.fresh) n_new += sl.n_tiles; }
     std::vector<int> at[MAX_XCD];
-    const bool persistent = round_fits(spread(S, at));
+    const bool persistent = !S.by_phases && round_fits(spread(S, at));
     int e;
     if (persistent) {
       e = persistent_round(S, ipr, at);
@@ -378,9 +404,7 @@ static void scheduler(Server* Sp) {
     // one transfer of every slot's state (unused slots are ignored below)
     if (!e) e = hipMemcpyAsync(S.h_solves, S.d_solves, sizeof(SolveDev) * S.slots.size(), hipMemcpyDeviceToHost, S.stream);
     if (!e) e = hipStreamSynchronize(S.stream);
-    if (!e && persistent)
-      for (const XcdCtl& x : ((const ServeRound*)S.h_round)->x)
-        if (x.error) e = hipErrorLaunchTimeOut;   // (the stall detector ended the launch)
+    if (!e && persistent && !check_round(S)) e = hipErrorLaunchFailure;
     if (e) { std::lock_guard<std::mutex> lk(S.mu); fail_locked(S, "round failed: " + std::string(hipGetErrorString((hipError_t)e))); break; }
     {
       // the admission copies have completed: the host arrays are free again
@@ -394,8 +418,8 @@ static void scheduler(Server* Sp) {
     for (size_t i = 0; i < S.slots.size(); ++i) {
       ServeSlot& sl = S.slots[i];
       if (!sl.used) continue;
-      sl.fresh = false;
       const SolveDev& d = S.h_solves[i];
+      sl.fresh = d.status == SOLVE_INIT;   // (a persistent round may not have run it)
       if (d.status < SOLVE_CONVERGED) continue;
       std::vector<double> x(sl.n);
       bool cp = hipMemcpyAsync(x.data(), d.x, sl.n * 8, hipMemcpyDeviceToHost, S.stream) == hipSuccess &&

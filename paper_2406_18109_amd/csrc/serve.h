@@ -68,4 +68,21 @@ struct ServeRound {
   int32_t iters;
 };
 
+// How a round ended: every solve run; or some XCD got no block and its solves
+// are as they were (an XCD of the list may have no block where the hardware's
+// ids are not 0 to n_xcd - 1); or some solve was begun and not settled.
+// given: the claims that the round started with, now: those it left.
+enum RoundEnd { ROUND_WHOLE, ROUND_UNSERVED, ROUND_BROKEN };
+inline RoundEnd round_end(const ServeRound& R, const int32_t* list, const ServeClaim* given, const ServeClaim* now) {
+  if (all_settled(R.x, R.n_xcd)) return ROUND_WHOLE;
+  for (uint32_t k = 0; k < R.n_xcd; ++k) {
+    if (R.x[k].n_settled == R.x[k].n_streams) continue;
+    for (uint32_t j = 0; j < R.x[k].n_streams; ++j) {
+      const int32_t i = list[R.x[k].first + j];
+      if (now[i].claim != given[i].claim || now[i].done != 0) return ROUND_BROKEN;
+    }
+  }
+  return ROUND_UNSERVED;
+}
+
 }  // namespace dfx
