@@ -1644,9 +1644,11 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
   // each candidate twice, interleaved, between two events; a timing is read
   // at the plan's next execution, so tuning adds no synchronisation of its
   // own.  A candidate replaces the default only if its faster run beats the
-  // default's by 3 %.  A graph being recorded takes the default shape.
+  // default's by 3 %.  A graph being recorded takes the default shape.  A
+  // pass with a block for every tile has no waves to give tiles to: it is not
+  // timed, and its plan keeps the default and its candidates.
   bool timed = false;
-  if (!p.tune_cand.empty() && !c.no_alloc && !c.batch_rec) {
+  if (!p.tune_cand.empty() && !c.no_alloc && !c.batch_rec && !coop_pass(p, c.cfg.jit != 0)) {
     const int nc = (int)p.tune_cand.size();
     if (p.tune_pending >= 0 && !c.capturing) {
       float ms = 0.f;
@@ -1790,6 +1792,18 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
   }
   const bool coop = coop_pass(p, fn != nullptr);
   if (coop) P.st_n = 0;   // (it reads every stream as it is)
+  if (timed) {
+    // timings of another kernel (the compiled one has become ready) say
+    // nothing of this one: it starts with a warm-up of its own
+    const int kernel = fn ? 1 : 0;
+    if (coop || (p.tune_kernel >= 0 && p.tune_kernel != kernel)) {
+      p.tune_ms.assign(p.tune_cand.size(), 3.0e38f);
+      p.tune_pending = -1;
+      p.tune_step = 1;
+      timed = false;
+    }
+    p.tune_kernel = kernel;
+  }
   // column shift (aligned output vectors), then row split, of passes
   // without reductions; either changes the launch shape only
   const int cs_shift = coop ? 0 : fn && ra_shift > 0 ? ra_shift : col_shift_for(p, P, es);

@@ -130,6 +130,7 @@ struct PassPlan {
   std::vector<float> tune_ms;       // fastest timing per candidate
   int tune_step = 0;          // execution count while tuning (0: the untimed warm-up)
   int tune_pending = -1;      // candidate whose events are in flight
+  int tune_kernel = -1;       // what the timings so far are of: 0 interpreted, 1 compiled
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   // compiled kernel of this pass (jit = 1 or 2): requested at the first
   // execution, shared by every plan with the same program and variant
