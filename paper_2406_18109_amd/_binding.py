@@ -103,6 +103,18 @@ SOLVE_QUEUED, SOLVE_RUNNING, SOLVE_CONVERGED, SOLVE_MAXITER, SOLVE_BREAKDOWN = 0
 _lib = None
 _fast = None
 
+
+class _CtypesOnly:
+    """In the place of the marshalling module where it is not built, or built
+    for another Python: no call is made natively, every one takes the ctypes
+    route (about 4 us a task more)."""
+
+    @staticmethod
+    def submit(*a):
+        return None
+
+    store_create = store_release = part_none = part_tiling = submit
+
 # name -> (restype, argtypes) for every exported call
 SIGNATURES = {
     "dfx_version": (C.c_char_p, []),
@@ -176,12 +188,16 @@ def lib():
         f.argtypes = args
     # the calls made per task are marshalled in C (csrc/marshal.cpp, built
     # with the library); bound once, before any context exists
-    from . import _marshal
-    _marshal.bind(tuple(C.cast(getattr(L, "dfx_" + n), C.c_void_p).value for n in
-                        ("submit", "store_create", "store_release", "proj_identity", "part_none", "part_tiling")),
-                  OPS, PRIV, DTYPES)
     global _fast
-    _fast = _marshal
+    try:
+        from . import _marshal
+    except ImportError:
+        _fast = _CtypesOnly
+    else:
+        _marshal.bind(tuple(C.cast(getattr(L, "dfx_" + n), C.c_void_p).value for n in
+                            ("submit", "store_create", "store_release", "proj_identity", "part_none", "part_tiling")),
+                      OPS, PRIV, DTYPES)
+        _fast = _marshal
     _lib = L
     return L
 

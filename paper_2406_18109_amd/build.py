@@ -96,15 +96,23 @@ def _compile(src: str, device: bool) -> str:
 
 
 def build_marshal() -> str:
-    """The binding's argument marshalling (csrc/marshal.cpp), a CPython extension."""
+    """The binding's argument marshalling (csrc/marshal.cpp), a CPython extension.
+    Without a C++ compiler or Python's headers there is none, and the binding
+    marshals through ctypes; returns "" then."""
     out = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
     tmp = out + ".tmp%d" % os.getpid()
     cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I" + sysconfig.get_paths()["include"],
            "-I" + os.path.join(ROOT, "include"), os.path.join(CSRC, "marshal.cpp"), "-o", tmp]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        sys.stderr.write(r.stdout + r.stderr)
-        raise RuntimeError("compile failed: marshal.cpp")
+    try:
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        msg = r.stdout + r.stderr if r.returncode else None
+    except OSError as e:
+        msg = str(e)
+    if msg is not None:
+        if os.path.exists(out):
+            os.remove(out)   # (of an older source)
+        sys.stderr.write("%s\nmarshal.cpp not built: calls go through ctypes\n" % msg)
+        return ""
     os.replace(tmp, out)
     return out
 
