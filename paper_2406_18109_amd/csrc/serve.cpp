@@ -282,12 +282,17 @@ static int64_t spread(const Server& S, std::vector<int> (&at)[MAX_XCD]) {
 // Whether the round runs as one persistent launch: the fullest XCD has at
 // most this many tiles.  There a phase is bound by latency, and costs less
 // than the phase launches; with more, those use the chip's bandwidth better.
-// Measured, an iteration persistent against phases: one solve of side 256
-// (16 tiles) 32 against 104 us, 512 (64) 71 against 109, 724 (128) 133
-// against 128, 1024 (256) 252 against 134; sixteen solves of side 256 (32
-// tiles an XCD) 78 against 155, of side 512 (128) 241 against 243.
+// Measured, an iteration persistent against phases, five-point matrices: one
+// solve of side 256 (16 tiles) 32 against 104 us, 512 (64) 71 against 109, 724
+// (128) 133 against 128, 1024 (256) 252 against 134; sixteen solves of side
+// 256 (32 tiles an XCD) 78 against 155, of side 512 (128) 241 against 243.
+// The line is the same for other matrices, whose entries either kind of round
+// reads: one solve of 112 tiles with 9 entries a row 182 against 188 us, with
+// 27 535 against 538; of 128 tiles with 9 198 against 190, 15 270 against 260,
+// 27 587 against 544 (51 and more are faster persistent there, 1114 against
+// 1758); of 64 tiles with 27 277 against 527.
 // DFX_SERVE_ROUND=0 or 1 forces one of the two.
-constexpr int64_t ROUND_MAX_TILES = 128;
+constexpr int64_t ROUND_MAX_TILES = 112;
 static bool round_fits(int64_t fullest) {
   const char* e = std::getenv("DFX_SERVE_ROUND");
   if (e && (e[0] == '0' || e[0] == '1')) return e[0] == '1';
