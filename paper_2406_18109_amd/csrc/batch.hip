@@ -263,13 +263,16 @@ __global__ __launch_bounds__(COOP_BLOCK) void batch_kernel(const BatchPass* __re
 
 }  // namespace
 
-// Allows the batch kernels the dynamic LDS of `lds` bytes and returns how
-// many of their blocks a compute unit holds with it (heavy: the
-// transcendental variant), 0 on failure.
+// Allows the batch kernels the dynamic LDS that any pass may need and returns
+// how many of their blocks a compute unit holds with `lds` bytes (heavy: the
+// transcendental variant), 0 on failure.  (The allowance belongs to the
+// kernel, not to the launch: one that followed each batch's need could be
+// lowered by another thread's batch between this one's setting and launch.)
 int batch_blocks_per_cu(int heavy, uint32_t lds) {
   int blocks = 0;
   const void* f = heavy ? (const void*)&batch_kernel<1> : (const void*)&batch_kernel<0>;
-  if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return 0;
+  if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)coop_lds(VM_MAXRED, true)) != hipSuccess)
+    return 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, f, COOP_BLOCK, lds) != hipSuccess) return 0;
   return blocks;
 }
