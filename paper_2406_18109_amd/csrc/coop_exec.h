@@ -147,12 +147,12 @@ __device__ __forceinline__ void coop_spmv(const PT& P, const int64_t base, T* yt
 }
 
 // Tile t of pass P (a VmParams, or any type with its fields) by every wave
-// of the block; lds: coop_lds_bytes, tot: VM_MAXRED values in LDS that
+// of the block; lds: coop_lds bytes, tot: VM_MAXRED values in LDS that
 // receive the tile's sums (from lane 0 of wave k; the caller's next barrier
 // publishes them).  The pass's global stores are issued, not waited for.
-template <typename T, int HV, int NW = COOP_WAVES, class PG = VmInterp, class PT>
+template <typename T, int HV, class PG = VmInterp, class PT>
 __device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* lds, T* tot) {
-  constexpr int RPW = RED_TH / NW;   // rows per wave
+  constexpr int RPW = COOP_RPW;
   // rows per step: two in arithmetic kernels; one in the transcendental ones
   // (their handlers need the registers: 1024 threads leave 128 per lane)
   typedef Shape<T, HV, false, VM_NREG_LIGHT, (HV > 0 ? 1 : 2)> S;
@@ -312,7 +312,7 @@ __device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* ld
   }
 }
 
-// One ordinary pass with a block of NW waves for every tile (the rule and its
+// One ordinary pass with a block of 16 waves for every tile (the rule and its
 // measurements: coop_pass in core.cpp), interpreted or compiled.  Bound: with
 // a wave per tile the chain of 32 rows' loads (and, in SpMV, the row walks)
 // of one wave; here a wave has two rows, the lane sums run in their order
@@ -320,11 +320,11 @@ __device__ __forceinline__ void coop_tile(const PT& P, const int64_t t, char* ld
 // over 150 cubed, 8 iterations: 4039 -> 2370 us).  The tile's sum has the
 // ordinary pass's bits; a lone block finishes its results itself
 // (red_direct), otherwise the block-sum reduction gets one sum per tile.
-template <typename T, int NW, class PG = VmInterp>
-__global__ __launch_bounds__(NW * WAVE) void coop_kernel(const VmParams P) {
+template <typename T, class PG = VmInterp>
+__global__ __launch_bounds__(COOP_BLOCK) void coop_kernel(const VmParams P) {
   extern __shared__ __attribute__((aligned(16))) char coop_dyn_lds[];
   __shared__ T tot[VM_MAXRED];
-  coop_tile<T, 0, NW, PG>(P, (int64_t)blockIdx.x, coop_dyn_lds, tot);
+  coop_tile<T, 0, PG>(P, (int64_t)blockIdx.x, coop_dyn_lds, tot);
   // (wave k holds reduction k's tile sum)
   const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
   if (wib < P.n_red && (threadIdx.x & (WAVE - 1)) == 0) {

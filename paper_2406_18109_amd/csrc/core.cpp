@@ -1497,6 +1497,15 @@ static int staged_streams(const PassPlan& p, size_t n_stores);
 //     7814 -> 7110, 380 cubed (13397) 16950 -> 15627.  A lone tile of one
 //     reduction stays with red_split, which spreads it over several blocks
 //     (CG 64: 209 against 232 us).
+//   compiled passes without SpMV, timed alone (the pass and its block sums): dot
+//     products of 5000 doubles 11.3 -> 5.8 us, 1e5 9.1 -> 6.3, 1e6 9.1 -> 6.9,
+//     5e6 28.4 -> 19.1, 3e7 97 -> 88, 6e7 181 -> 167; of 5e6 floats 14.3 ->
+//     12.0, 3e7 55.9 -> 39.6, 1.2e8 185 -> 172; sums of 3e7 doubles 86.6 ->
+//     45.9; two reductions of 3e7 115 -> 95.  Tables, whose ragged strips a
+//     block reads element by element: sums of squares of 50021 rows of 33, 100,
+//     300, 1000 and 1001 floats 38.6 -> 19.4, 36.7 -> 19.4, 62.8 -> 32.9, 120 ->
+//     70.7, 126 -> 71.3 us; 20000 x 101 doubles, two reductions, 22.3 -> 12.2.
+//     (Behind: a dot of 8000 x 1000 floats, 1000 tiles, 19.3 -> 23.3.)
 //   stencil-staged passes (three Jacobi sweeps; a block reads the shifted
 //     views from L2 instead of staging them, which pays while the chip is not
 //     full): interpreted 400^2 (52 tiles) 161 -> 99 us, 2000^2 (1008) 225 ->
@@ -1507,8 +1516,13 @@ static int staged_streams(const PassPlan& p, size_t n_stores);
 //     against rows staged through LDS): compiled, multigrid V-cycles over
 //     511^2 unknowns (64 tiles on the finest level) 2139 -> 2216 us, 1023^2
 //     (256) 3064 -> 2912, 2047^2 3096 -> 2910, 4095^2 8525 -> 7750;
-//     interpreted 1023^2 3693 -> 3587 but 2047^2 3440 -> 3471.
-// Two reductions are what 64 KB of LDS hold.  Above NOALLOC_BLOCKS tiles the
+//     interpreted 1023^2 3693 -> 3587 but 2047^2 3440 -> 3471.  Alone, with a
+//     subtraction: 2^20 rows (256 tiles) of 1, 3, 5, 9 and 27 entries 17.0 ->
+//     10.2, 20.7 -> 13.5, 24.9 -> 17.0, 41.7 -> 38.8, 256 -> 169 us; 4e6 rows of
+//     5 82.5 -> 66.2, 1.6e7 302 -> 265; floats, 2e6 rows of 5, 26.8 -> 26.7.
+//     (Between 64 and 256 tiles nothing was timed.)
+// Two reductions take 64 KB of LDS, the most a launch gets without raising its
+// kernel's allowance.  Above NOALLOC_BLOCKS tiles the
 // block sums would no longer fit the fixed scratch.  DFX_COOP=0 turns it off.
 constexpr int64_t COOP_VM_TILES = 512, COOP_VM_SPMV_TILES = 1024;
 constexpr int64_t COOP_STENCIL_TILES = 512, COOP_VM_STENCIL_TILES = 1024;
@@ -1535,9 +1549,11 @@ static bool coop_pass(const PassPlan& p, bool compiled) {
 // limit at 256; 4096 gave 0.82 ms as well); stencil-staged passes (the 8192^2 Jacobi
 // sweep: 0.46 against 0.51 ms); passes with a value broadcast along each row
 // (a table of 50021 x 1001 FP32 scaled per column and row: 129 instead of
-// 354 us, its accesses being element by element in the interpreter).  Large arithmetic and staged-SpMV passes
-// stream at the interpreter's rate or slightly below it compiled (the CG
-// 256^3 SpMV + dot: 438 against 390 us) and stay interpreted.
+// 354 us, its accesses being element by element in the interpreter); passes
+// with a block for every tile (coop_pass: reductions, and large SpMVs, among
+// them the CG 256^3 SpMV + dot, which the ordinary kernel ran slower compiled,
+// 438 against 390 us).  Other large arithmetic passes stream at the
+// interpreter's rate and stay interpreted.
 // DFX_JIT_ALL=1 compiles every pass.
 static bool jit_wanted(const PassPlan& p, int st_n) {
   const char* all = std::getenv("DFX_JIT_ALL");
@@ -1577,7 +1593,7 @@ static std::shared_ptr<JitEntry> request_compiled(PassPlan& p, int st_n, int row
     }
   JitVariant v = jit_variant(p.dtype == DFX_F64, p.tier, (int)p.ins.size(), p.kind == 1, st_n, rows);
   p.jit_coop = coop_pass(p, true);
-  if (p.jit_coop) v.coop = COOP_WAVES;
+  v.coop = p.jit_coop;
   std::string name;
   const std::string src = jit_source(v, g, &name);
   return jit_request(src, name, sync);
@@ -1751,7 +1767,10 @@ static int run_pass(Ctx& c, PassPlan& p, const std::vector<int64_t>& order) {
     const char* st = std::getenv("DFX_SPMV_STAGE");
     P.sp_stage = st && (st[0] == '0' || st[0] == '1') ? st[0] == '1' : p.n_tiles >= 256;
     // a one-tile pass is one block: its four waves compute the rows together
-    // (DFX_SPMV_COOP=0 or 1 overrides)
+    // (DFX_SPMV_COOP=0 or 1 overrides).  What still runs so: a pass that
+    // coop_pass refuses and no split below takes (transcendental, with three
+    // or four reductions, with more than six streams or a stride, or of one
+    // row without reductions)
     const char* co = std::getenv("DFX_SPMV_COOP");
     P.sp_coop = (p.n_tiles == 1 && p.grid == 1) &&
                 (co && (co[0] == '0' || co[0] == '1') ? co[0] == '1' : true);

@@ -350,7 +350,7 @@ std::string jit_source(const JitVariant& v, const JitProgram& g, std::string* na
   for (const VmInstr& I : g.code) put_instr(s, I, f64);
   s += "#undef DFX_I\n  }\n};\n\n}  // namespace dfx\n";
   char ne[256];
-  if (v.coop) std::snprintf(ne, sizeof(ne), "dfx::coop_kernel<%s, %d, dfx::JitPass>", f64 ? "double" : "float", v.coop);
+  if (v.coop) std::snprintf(ne, sizeof(ne), "dfx::coop_kernel<%s, dfx::JitPass>", f64 ? "double" : "float");
   else std::snprintf(ne, sizeof(ne), "dfx::vm_kernel<%s, %d, %s, %d, %d, %d, %s, dfx::JitPass>", f64 ? "double" : "float",
                 v.hv, v.spmv ? "true" : "false", v.nr, v.nb, v.rows, v.sten ? "true" : "false");
   if (name_expr) *name_expr = ne;

@@ -37,7 +37,7 @@ struct JitVariant {
   int rows = 0;    // rows per step (0: the kernel's rule)
   int spmv = 0;
   int sten = 0;    // stencil staging variant
-  int coop = 0;    // a block of this many waves per tile (coop_kernel), 0: vm_kernel
+  bool coop = false; // a block of 16 waves per tile (coop_kernel)
   int waves = 2;   // waves-per-SIMD target given to the compiler
   int reload = -1;  // parameters reloaded at every step (step_params): 1, 0, -1 the default rule
 };

@@ -214,8 +214,7 @@ inline size_t vm_dyn_lds_bytes(const VmParams& P, bool sten) {
                              : 0;
 }
 
-// A tile run by a whole block (coop_exec.h): 16 waves of two rows each in the
-// persistent executors, NW of them in coop_kernel.
+// A tile run by a whole block (coop_exec.h): 16 waves of two rows each.
 constexpr int COOP_BLOCK = 1024;
 constexpr int COOP_WAVES = COOP_BLOCK / WAVE;
 constexpr int COOP_RPW = RED_TH / COOP_WAVES;   // tile rows per wave
