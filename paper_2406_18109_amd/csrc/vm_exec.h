@@ -606,9 +606,11 @@ __device__ __forceinline__ void vm_step(
       }
     }
     if (split) {
+      // (padding slots too: left by a run-time bound, the loop is not unrolled
+      // for ten streams and the values go to scratch)
 #pragma unroll
       for (int a = 0; a < NINB; ++a) {
-        if (a >= n_in_of<PG>(P)) break;
+        if (PG::COMPILED && a >= n_in_of<PG>(P)) break;
         if (PG::COMPILED && PG::bcol[a]) continue;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
