@@ -327,6 +327,16 @@ template <class PG> __device__ __forceinline__ int n_out_of(const VmParams& P) {
   return PG::COMPILED ? PG::N_OUT : P.n_out;
 }
 
+// Where a split vector's elements are picked: in the loaded values (L), or as
+// the step moves them to the register file.  The first puts copies and a wait
+// into every step of the interpreter's kernels of doubles (1048576 doubles
+// times a constant 9.2 us instead of 8.6), the second registers into those of
+// floats with up to two streams (a dot product of 3e8 436 instead of 411 us);
+// realigning passes move L about anyway (a copy into the interior of a 6000^2
+// grid 128 against 142 us).
+template <typename T, int NINB, class PG>
+constexpr bool edge_in_place = PG::REALIGN || (sizeof(T) == 4 && NINB == 2 && !PG::COMPILED);
+
 // Vector-mode loads of one step (MODE_FAST or MODE_EDGE) into L: every
 // stream's loads issued back to back before the first wait.  Padding slots
 // of the stream bucket are not loaded: their registers are free registers of
@@ -402,8 +412,7 @@ __device__ __forceinline__ void vm_load(const VmParams& P, T (&L)[NINB][E], int6
       for (int v = 0; v < V; ++v) L[a][u * V + v] = w[v];
     }
   }
-  // (elsewhere the step picks the elements: see vm_step)
-  if constexpr (PG::REALIGN)
+  if constexpr (edge_in_place<T, NINB, PG>)
     if (mode == MODE_EDGE) {
 #pragma unroll
       for (int a = 0; a < NINB; ++a) {
@@ -508,12 +517,7 @@ __device__ __forceinline__ void vm_step(
     }
   } else if (mode != MODE_SLOW && SPLIT) {
     // issued by the caller (or prefetched by the previous step) into L
-    // (a lane across the edge picks its elements here: done in place in L, it
-    // put copies and a wait into every step, 1048576 doubles times a constant
-    // 9.2 us instead of 8.6; realigning passes, which move L about anyway, are
-    // better in place, a copy into the interior of a 6000^2 grid 128.2 against
-    // 141.6 us)
-    if (split && !PG::REALIGN) {
+    if (split && !edge_in_place<T, NINB, PG>) {
 #pragma unroll
       for (int a = 0; a < NINB; ++a) {
         if (a >= n_in_of<PG>(P)) break;
