@@ -1571,8 +1571,9 @@ static std::shared_ptr<JitEntry> request_compiled(PassPlan& p, int st_n, int row
   g.n_in = (int)p.ins.size();
   g.n_out = (int)p.outs.size();
   g.n_red = (int)p.red_cstore.size();
-  // (one-dimensional: only the last steps are ragged; leaving the edge loads
-  // out took FP64 Black-Scholes over 2^26 options from 689 to 685 us)
+  // (one-dimensional: only the last steps are ragged, and with the edge loads
+  // in FP64 Black-Scholes over 2^26 options takes 698 to 701 us instead of 696
+  // to 697)
   g.line = p.is1d && p.tier != TIER_ARITH;
   // (a stencil-staged kernel keeps the code it cannot reach: without it the
   // compiler takes 163 registers instead of 120 for the Jacobi update, and
