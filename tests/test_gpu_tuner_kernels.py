@@ -39,7 +39,8 @@ c.close()
 def _runs(tmp_path, op, n, jit, before=0):
     """Execution at which the pass's shape was decided (None: never), and how
     many compiled launches there were at the wait and at the end."""
-    env = dict(os.environ, DFX_TRACE="1", DFX_JIT_CACHE=str(tmp_path))
+    env = dict(os.environ, DFX_TRACE="1", DFX_JIT_CACHE=str(tmp_path), DFX_COOP="1")
+    env.pop("DFX_JIT", None)
     p = subprocess.run([sys.executable, "-c", CHILD, ROOT, op, str(n), str(jit), str(before)], env=env, text=True,
                        capture_output=True, timeout=100)
     assert p.returncode == 0, p.stderr[-2000:]
