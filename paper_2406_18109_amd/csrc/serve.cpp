@@ -262,21 +262,23 @@ static int phase_round(Server& S, int ipr, size_t n_all, size_t n_new) {
 // The resident solves spread over the XCDs, largest first, each to the XCD
 // with the fewest tiles so far (a solve's result does not depend on where it
 // runs).  Returns the tiles of the fullest XCD.
-static int64_t spread(const Server& S, std::vector<int> (&at)[MAX_XCD]) {
+static int64_t spread(const Server& S, std::vector<int> (&at)[MAX_XCD], XcdLoad (&load)[MAX_XCD]) {
   const int n_xcd = std::max(1, std::min(MAX_XCD, S.n_cu / 32));
   std::vector<int> order;
   for (size_t i = 0; i < S.slots.size(); ++i)
     if (S.slots[i].used) order.push_back((int)i);
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return S.slots[a].n_tiles > S.slots[b].n_tiles; });
-  int64_t load[MAX_XCD] = {};
   for (int i : order) {
     int x = 0;
     for (int k = 1; k < n_xcd; ++k)
-      if (load[k] < load[x]) x = k;
-    load[x] += S.slots[i].n_tiles;
+      if (load[k].tiles < load[x].tiles) x = k;
+    load[x].tiles += S.slots[i].n_tiles;
+    load[x].solves += 1;
     at[x].push_back(i);
   }
-  return *std::max_element(load, load + n_xcd);
+  int64_t fullest = 0;
+  for (int k = 0; k < n_xcd; ++k) fullest = std::max(fullest, load[k].tiles);
+  return fullest;
 }
 
 // Whether the round runs as one persistent launch: the fullest XCD has at
@@ -299,15 +301,16 @@ static bool round_fits(int64_t fullest) {
   return fullest <= ROUND_MAX_TILES;
 }
 
-// Blocks of a persistent round: one per compute unit (any number runs every
-// solve of the XCDs it reaches; DFX_SERVE_BLOCKS=<n> sets it).
-static int round_blocks(const Server& S) {
-  const char* e = std::getenv("DFX_SERVE_BLOCKS");
-  return std::max(1, e ? std::min(std::atoi(e), S.n_cu) : S.n_cu);
+// Blocks of a persistent round (DFX_SERVE_BLOCKS=<n> sets them: any number
+// runs every solve of the XCDs that it reaches).
+static int round_blocks(const Server& S, const XcdLoad* load) {
+  if (const char* e = std::getenv("DFX_SERVE_BLOCKS")) return std::max(1, std::min(std::atoi(e), S.n_cu));
+  const int n_xcd = std::max(1, std::min(MAX_XCD, S.n_cu / 32));
+  return n_xcd * blocks_per_xcd(load, n_xcd, S.n_cu / n_xcd);
 }
 
 // The round as one persistent launch.
-static int persistent_round(Server& S, int ipr, const std::vector<int> (&at)[MAX_XCD]) {
+static int persistent_round(Server& S, int ipr, const std::vector<int> (&at)[MAX_XCD], const XcdLoad* load) {
   const size_t ms = S.slots.size();
   ServeRound* R = (ServeRound*)S.h_round;
   ServeClaim* claims = (ServeClaim*)(S.h_round + sizeof(ServeRound));
@@ -332,7 +335,7 @@ static int persistent_round(Server& S, int ipr, const std::vector<int> (&at)[MAX
   if (!e)
     e = launch_serve_round(S.d_solves, (ServeClaim*)(S.d_round + sizeof(ServeRound)),
                            (const int32_t*)(S.d_round + sizeof(ServeRound) + ms * sizeof(ServeClaim)),
-                           (ServeRound*)S.d_round, round_blocks(S), S.stream);
+                           (ServeRound*)S.d_round, round_blocks(S, load), S.stream);
   if (!e) e = hipMemcpyAsync(S.h_round, S.d_round, sizeof(ServeRound), hipMemcpyDeviceToHost, S.stream);
   S.stats.launches += 1;
   return e;
@@ -398,10 +401,12 @@ static void scheduler(Server* Sp) {
     for (auto& sl : S.slots)
       if (sl.used) { n_all += sl.n_tiles; if (sl.fresh) n_new += sl.n_tiles; }
     std::vector<int> at[MAX_XCD];
-    const bool persistent = !S.by_phases && round_fits(spread(S, at));
+    XcdLoad load[MAX_XCD] = {};
+    const int64_t fullest = spread(S, at, load);
+    const bool persistent = !S.by_phases && round_fits(fullest);
     int e;
     if (persistent) {
-      e = persistent_round(S, ipr, at);
+      e = persistent_round(S, ipr, at, load);
     } else {
       if (!grow_items(S, n_all + n_new)) { std::lock_guard<std::mutex> lk(S.mu); fail_locked(S, "work list allocation failed"); break; }
       e = phase_round(S, ipr, n_all, n_new);

@@ -85,4 +85,31 @@ inline RoundEnd round_end(const ServeRound& R, const int32_t* list, const ServeC
   return ROUND_UNSERVED;
 }
 
+// Blocks of a round on each XCD: as many as the fullest one has tiles, and at
+// most seven eighths of its compute units, unless a solve alone on its XCD
+// then takes its tiles in one pass more (solves that share one fill in for
+// each other).  A block holds its compute unit for the whole round; with one
+// on every unit, the device's other streams waited for rounds to end.  Beside
+// sixteen solves of 16 tiles, with phase launches, with blocks of 116
+// registers on every unit, and as here with 96 registers: ten CG iterations
+// over 300^2 0.88, 6.2 and 0.62 ms, four Jacobi sweeps of 4096^2 0.73, 4.3 and
+// 1.45, eight scaled copies of 2^24 doubles 0.65, 3.8 and 1.6; beside one such
+// solve the CG 0.66, 3.7 and 0.44.  The fewer registers alone: 5.0, 1.43 and
+// 2.2 ms beside the sixteen.  48 requests take 47.6 ms with every unit, 47.6
+// with seven eighths, 48.3 with three quarters and 54.5 with half; one solve
+// of 32 tiles 36.5 us an iteration with 32 blocks, 51.6 with 28.
+struct XcdLoad { int64_t tiles; int32_t solves; };
+inline int blocks_per_xcd(const XcdLoad* load, int n_xcd, int units) {
+  const int64_t few = units - units / 8;
+  int64_t fullest = 1;
+  bool all = false;
+  for (int x = 0; x < n_xcd; ++x) {
+    const int64_t t = load[x].tiles;
+    if (t > fullest) fullest = t;
+    if (load[x].solves == 1 && (t + few - 1) / few > (t + units - 1) / units) all = true;
+  }
+  const int64_t most = all ? units : few;
+  return (int)(fullest < most ? fullest : most);
+}
+
 }  // namespace dfx

@@ -351,7 +351,9 @@ struct ServeItem {
 // tile stay with their block for the whole round.  The phase launches this
 // replaces there (seven an iteration, one wave per tile) left most of the chip
 // idle: 48 solves of sides 32 to 256 to 1e-8 took 111 ms, against 48 ms.
-__global__ __launch_bounds__(COOP_BLOCK) void serve_round_kernel(SolveDev* __restrict__ solves,
+// (Five waves per SIMD: a block's four leave room for another stream's; 96
+// registers instead of 116, and no slower.)
+__global__ __launch_bounds__(COOP_BLOCK) __attribute__((amdgpu_waves_per_eu(5))) void serve_round_kernel(SolveDev* __restrict__ solves,
                                                                  ServeClaim* __restrict__ claims,
                                                                  const int32_t* __restrict__ list,
                                                                  ServeRound* __restrict__ ctl) {
